@@ -1029,6 +1029,256 @@ static hipError_t run_dma(const ConvArgs &a, hipStream_t st) {
 }
 
 // ---------------------------------------------------------------------------
+// Dense convolution for layers whose whole output is at most a few thousand
+// 16 x 16 tiles (one image or a few): what bounds them is latency.  The
+// shared tiles of the other kernels leave most CUs without a workgroup there
+// and pay a barrier and an exposed load per K step.  Here a wave owns 16
+// channels x 16 pixels and shares nothing: it streams its filter and pixel
+// rows through a private ring of LDS slots (conv_dma's rows, swizzle and
+// DMAs; no barrier, only vmcnt waits) and moves the next step's fragments to
+// registers while the current step runs on the matrix core.  Loading the
+// fragments straight into registers instead was slower (16 rows per load:
+// 64 cache-line lookups against 8 for a DMA of whole 128-byte rows).
+// Consecutive workgroups take consecutive channel tiles of the same pixels,
+// so with a multiple of 8 channel tiles each XCD's L2 holds an eighth of
+// the filters.
+// The k order is that of the kernel the layer takes at larger batches, MFMA
+// by MFMA, so an image's result does not depend on the batch: (r, s, c)
+// with channels fastest, or, PLANE (conv_img's layers), 64-channel planes
+// outermost.  UNI: a tap is a whole number of steps, so the tap is the same
+// for the whole wave.  SPLIT: one wave per k range of a split layer; the
+// first wave adds the ranges' partial sums in range order, as splitk_reduce
+// does.
+// ---------------------------------------------------------------------------
+template <typename T, bool PLANE, bool UNI, int SPLIT>
+__global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
+    constexpr int ES = (int)sizeof(T);
+    constexpr int VEC = 16 / ES;                 // k per 16-byte chunk
+    constexpr int KS = 128 / ES;                 // k per step
+    // slots: PLANE unrolls a plane's 9 taps over 9 of them
+    constexpr int NS = PLANE ? 9 : 4;
+    constexpr int STAGE = 4096;                  // 16 filter rows, 16 pixel rows
+    static_assert(!PLANE || (ES == 2 && UNI && SPLIT == 1), "planes are fp16");
+    __shared__ __attribute__((aligned(16))) char lds[SPLIT * NS * STAGE];
+    const int nt = (a.N + 15) / 16;
+    const int n0 = (int)(blockIdx.x % nt) * 16, m0 = (int)(blockIdx.x / nt) * 16;
+    const int M = a.nimg * a.P * a.Q;
+    const int lane = threadIdx.x & 63;
+    const int range = SPLIT > 1 ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : 0;
+    char *ring = lds + range * NS * STAGE;
+    const int Ktot = a.R * a.S * a.Cs;
+    const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * a.Cs * ES);
+    const Rsrc wr = make_rsrc(a.w, (long)a.N * Ktot * ES);
+
+    // A DMA fills 8 rows; this lane's row of each and its (swizzled) chunk
+    const int lrow = lane >> 3, chunk = (lane & 7) ^ lrow;
+    int wrow[2], pix[2], ih0[2], iw0[2];
+#pragma unroll
+    for (int i = 0; i < 2; i++) {
+        const int n = n0 + i * 8 + lrow;
+        wrow[i] = n < a.N ? n * Ktot * ES : OOB;
+        const int m = m0 + i * 8 + lrow;
+        const int q = m % a.Q, u = m / a.Q, p = u % a.P, img = u / a.P;
+        ih0[i] = m < M ? p * a.stride - a.pad : -0x40000000;
+        iw0[i] = q * a.stride - a.pad;
+        pix[i] = m < M ? ((img * a.H + ih0[i]) * a.W + iw0[i]) * a.Cs * ES : 0;
+    }
+    auto in_map = [&](int i, int r, int s) {
+        return (unsigned)(ih0[i] + r) < (unsigned)a.H && (unsigned)(iw0[i] + s) < (unsigned)a.W;
+    };
+    const int fr = lane & 15, fg = lane >> 4;
+    const int c0 = fr * 128 + (fg ^ (fr & 7)) * 16, c1 = fr * 128 + ((4 + fg) ^ (fr & 7)) * 16;
+    u32x4 wf[2][2], pf[2][2];                    // [buffer][half step]
+    auto read = [&](const char *st, int b) {
+#pragma unroll
+        for (int kk = 0; kk < 2; kk++) {
+            wf[b][kk] = *(const u32x4 *)(st + (kk ? c1 : c0));
+            pf[b][kk] = *(const u32x4 *)(st + 2048 + (kk ? c1 : c0));
+        }
+    };
+    f32x4 acc = (f32x4)(0.f);
+    auto mfma = [&](int b) {
+#pragma unroll
+        for (int kk = 0; kk < 2; kk++) {
+            if constexpr (ES == 2) {
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                    __builtin_bit_cast(f16x8, wf[b][kk]), __builtin_bit_cast(f16x8, pf[b][kk]),
+                    acc, 0, 0, 0);
+            } else {
+                const f32x4 w = __builtin_bit_cast(f32x4, wf[b][kk]);
+                const f32x4 x = __builtin_bit_cast(f32x4, pf[b][kk]);
+#pragma unroll
+                for (int t = 0; t < 4; t++)
+                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w[t], x[t], acc, 0, 0, 0);
+            }
+        }
+    };
+    // the reads of the slot that the next DMAs refill are done
+    auto drained = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt 0
+        asm volatile("" ::: "memory");
+    };
+    // step s + 1's slot has landed: at most NS - 1 later steps in flight
+    auto landed = [&]() {
+        wait_vmcnt<4 * (NS - 1)>();
+        asm volatile("" ::: "memory");
+    };
+
+    if constexpr (PLANE) {
+        // offsets of the 9 taps of plane 0; planes advance in the scalar
+        // offset, which stays inside the buffers
+        int xo[9][2];
+#pragma unroll
+        for (int t = 0; t < 9; t++)
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+                xo[t][i] = in_map(i, t / 3, t % 3)
+                               ? pix[i] + ((t / 3 * a.W + t % 3) * a.Cs) * 2 + chunk * 16
+                               : OOB;
+        int wo[2];
+#pragma unroll
+        for (int i = 0; i < 2; i++) wo[i] = wrow[i] != OOB ? wrow[i] + chunk * 16 : OOB;
+        auto issue = [&](int plane, int t) {
+            char *st = ring + t * STAGE;
+            const int so = plane * 128, sw = so + t * a.Cs * 2;
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (LdsPtr)(st + i * 1024), 16, wo[i],
+                                                         sw, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 2; i++)
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (LdsPtr)(st + 2048 + i * 1024), 16,
+                                                         xo[t][i], so, 0, 0);
+        };
+        const int planes = a.Cs / 64;
+#pragma unroll
+        for (int t = 0; t < 9; t++) issue(0, t);
+        landed();
+        read(ring, 0);
+        // one plane: 9 steps, so the fragment buffer alternates with the
+        // plane's parity; LAST: nothing left to issue
+        auto plane_steps = [&](int plane, auto par, auto last) {
+            constexpr int B = decltype(par)::value;
+            if constexpr (decltype(last)::value) wait_vmcnt<0>();
+#pragma unroll
+            for (int t = 0; t < 9; t++) {
+                drained();
+                if constexpr (!decltype(last)::value) {
+                    issue(plane + 1, t);
+                    landed();
+                }
+                if (!decltype(last)::value || t < 8)
+                    read(ring + (t == 8 ? 0 : t + 1) * STAGE, (B + t + 1) & 1);
+                mfma((B + t) & 1);
+            }
+        };
+        typedef std::integral_constant<int, 0> Even;
+        typedef std::integral_constant<int, 1> Odd;
+        int c = 0;
+        for (; c + 2 < planes; c += 2) {
+            plane_steps(c, Even(), std::false_type());
+            plane_steps(c + 1, Odd(), std::false_type());
+        }
+        if (c + 1 < planes) {
+            plane_steps(c, Even(), std::false_type());
+            plane_steps(c + 1, Odd(), std::true_type());
+        } else {
+            plane_steps(c, Even(), std::true_type());
+        }
+    } else {
+        const int nsteps = (Ktot + KS - 1) / KS;
+        const int sbeg = (int)((long)range * nsteps / SPLIT);
+        const int cnt = (int)((long)(range + 1) * nsteps / SPLIT) - sbeg;
+        // The next step to load: its tap (kr, ks) and channel kc.  UNI: the
+        // lane's offsets only advance by 128 bytes until the tap changes;
+        // an OOB offset stays out of range as it advances.  Else per lane,
+        // chunk by chunk.
+        const int kbeg = sbeg * KS + (UNI ? 0 : chunk * VEC);
+        int kc = kbeg % a.Cs, ks = kbeg / a.Cs % a.S, kr = kbeg / a.Cs / a.S;
+        int wo[2], xo[2];
+        auto set_tap = [&]() {
+            const bool ok = kr < a.R;
+            const int c = (UNI ? chunk * 16 : 0) + kc * ES;
+            const int xt = (kr * a.W + ks) * a.Cs * ES + c, wt = (kr * a.S + ks) * a.Cs * ES + c;
+#pragma unroll
+            for (int i = 0; i < 2; i++) {
+                wo[i] = ok && wrow[i] != OOB ? wrow[i] + wt : OOB;
+                xo[i] = ok && in_map(i, kr, ks) ? pix[i] + xt : OOB;
+            }
+        };
+        if constexpr (UNI) set_tap();
+        auto issue = [&](int slot) {
+            char *st = ring + slot * STAGE;
+            if constexpr (!UNI) set_tap();
+#pragma unroll
+            for (int i = 0; i < 2; i++) dma16(wr, st + i * 1024, wo[i]);
+#pragma unroll
+            for (int i = 0; i < 2; i++) dma16(xr, st + 2048 + i * 1024, xo[i]);
+            kc += KS;
+            if constexpr (UNI) {
+#pragma unroll
+                for (int i = 0; i < 2; i++) {
+                    wo[i] += 128;
+                    xo[i] += 128;
+                }
+                if (kc == a.Cs) {
+                    kc = 0;
+                    if (++ks == a.S) { ks = 0; ++kr; }
+                    set_tap();
+                }
+            } else {
+                while (kc >= a.Cs) {
+                    kc -= a.Cs;
+                    if (++ks == a.S) { ks = 0; ++kr; }
+                }
+            }
+        };
+        // (steps past the range load data that is never used, or zeros past
+        // the layer's end)
+#pragma unroll
+        for (int s = 0; s < NS; s++) issue(s);
+        landed();
+        read(ring, 0);
+        for (int s = 0; s < cnt; s += NS) {
+#pragma unroll
+            for (int b = 0; b < NS; b++) {
+                drained();
+                issue(b);
+                landed();
+                read(ring + (b + 1) % NS * STAGE, (b + 1) & 1);
+                if (s + b < cnt) mfma(b & 1);
+            }
+        }
+        // no DMA of this workgroup may land after its LDS is released
+        wait_vmcnt<0>();
+    }
+    if constexpr (SPLIT > 1) {
+        __shared__ f32x4 part[SPLIT - 1][64];
+        if (range > 0) part[range - 1][lane] = acc;
+        __syncthreads();
+        if (range > 0) return;
+#pragma unroll
+        for (int s = 1; s < SPLIT; s++) acc += part[s - 1][lane];
+    }
+    // conv_dma's epilogue arithmetic on 4 channels of one pixel per lane
+    const int n = n0 + fg * 4, m = m0 + fr;
+    if (n >= a.N || m >= M) return;
+    const size_t o = (size_t)m * a.N + n;
+    f32x4 v = acc * *(const f32x4 *)(a.scale + n) + *(const f32x4 *)(a.shift + n);
+    typedef typename Vec4<T>::t V4;
+    if (a.res) {
+        const V4 rv = *(const V4 *)((const T *)a.res + o);
+#pragma unroll
+        for (int e = 0; e < 4; e++) v[e] += to_f(rv[e]);
+    }
+    V4 ov;
+#pragma unroll
+    for (int e = 0; e < 4; e++) ov[e] = from_f<T>(a.relu ? relu_nan(v[e]) : v[e]);
+    *(V4 *)((T *)a.y + o) = ov;
+}
+
+// ---------------------------------------------------------------------------
 // fp16 implicit-GEMM convolution with a ping-pong wave schedule (dense
 // layers with at least 64 input channels).  Same GEMM view, operand roles,
 // LDS-DMA staging and row swizzle as conv_dma, for a 256-pixel x BN-channel
@@ -2132,6 +2382,8 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
     return bm128 ? D_128x128 : D_64x128;
 }
 
+static bool img_cfg(ConvCfg c) { return c == IMG_7 || c == IMG_14 || c == IMG_7S2; }
+
 static bool pool_cfg(ConvCfg c) {
     return c == PP_256_P8 || c == PP_256_P16 || c == D_128x64_P16 || c == D_128x128_P16 ||
            c == H_128x64_P16;
@@ -2143,9 +2395,42 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
     return pool_cfg(select_conv(dt, b));
 }
 
+// Whether a layer that select_conv gives to `c` runs on conv_lat at this
+// batch: up to 2048 tiles of 16 pixels x 16 channels, 8 per CU.  Measured
+// there, own kernel -> conv_lat: fp16, one image, 56x56x64 3x3 (784 tiles)
+// 11.3 -> 5.8 us, 28x28x128 (392) 15.5 -> 6.1, 14x14x256 (208) 28.3 -> 5.7,
+// 7x7x512 (128) 15.4 -> 8.3; fp32 28x28x128 32.2 -> 10.5, 14x14x256 59.1 ->
+// 16.3; near the line 56x56x64 11.4 -> 7.1 (two images, 1568 tiles),
+// 14x14x256 28.7 -> 13.4 (eight, 1664), fp32 56x56x64 19.2 -> 10.6.  Above
+// it the tiles that share rows win back what they lose in latency: 56x56x64
+// 11.6 = 11.6 at 3136 tiles, 28x28x72 -> 136 10.8 -> 14.7 at 3528, 14x14 96
+// -> 576 1x1 5.7 -> 9.3 at 3600.  conv_pw's layers, short in k, only up to
+// 1024: 96 -> 576 4.6 against 5.4 at 468 and 5.6 against 5.5 us at 1800.
+static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
+    const int es = dt == DT_F32 ? 4 : 2;
+    if (a.pool || (c < D_64x32 && c != PW_F16 && c != PP_256 && !img_cfg(c))) return false;
+    if (a.Cs % (16 / es) || (long)a.nimg * a.H * a.W * a.Cs * es >= (1l << 31) ||
+        (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
+        return false;
+    const long M = (long)a.nimg * a.P * a.Q;
+    return (M + 15) / 16 * ((a.N + 15) / 16) <= (c == PW_F16 ? 1024 : 2048);
+}
+
 const char *conv_kernel_name(int dt, const ConvArgs &a) {
     const bool f = dt == DT_F32;
-    switch (select_conv(dt, a)) {
+    const ConvCfg cfg = select_conv(dt, a);
+    if (lat_ok(dt, a, cfg)) {
+        if (img_cfg(cfg)) return "conv_lat<_Float16, true, true, 1>";
+        const bool uni = a.Cs % (f ? 32 : 64) == 0;
+        if (a.part && conv_splitk(dt, a) > 1)
+            return f ? (uni ? "conv_lat<float, false, true, 4>" : "conv_lat<float, false, false, 4>")
+                     : (uni ? "conv_lat<_Float16, false, true, 4>"
+                            : "conv_lat<_Float16, false, false, 4>");
+        return f ? (uni ? "conv_lat<float, false, true, 1>" : "conv_lat<float, false, false, 1>")
+                 : (uni ? "conv_lat<_Float16, false, true, 1>"
+                        : "conv_lat<_Float16, false, false, 1>");
+    }
+    switch (cfg) {
     case F32_N16: return "conv_igemm<float, 4, 128, 16, 4, 1>";
     case F32_N32: return "conv_igemm<float, 4, 128, 32, 4, 1>";
     case F32_N64: return "conv_igemm<float, 4, 64, 64, 2, 2>";
@@ -2220,6 +2505,28 @@ int conv_splitk(int dt, const ConvArgs &a) {
     return K >= 4096 && PQ <= 64 ? 4 : 1;
 }
 
+template <typename T>
+static hipError_t run_lat(const ConvArgs &a, bool plane, hipStream_t st) {
+    const long M = (long)a.nimg * a.P * a.Q;
+    const dim3 grid((unsigned)((M + 15) / 16 * ((a.N + 15) / 16)));
+    const bool uni = a.Cs % (128 / (int)sizeof(T)) == 0;
+    if (a.ksplit == 4) {
+        if (uni) launch(conv_lat<T, false, true, 4>, grid, dim3(256), st, a);
+        else launch(conv_lat<T, false, false, 4>, grid, dim3(256), st, a);
+        return hipGetLastError();
+    }
+    if (a.ksplit != 1) return hipErrorInvalidValue;
+    if (plane) {
+        if constexpr (sizeof(T) == 2) launch(conv_lat<T, true, true, 1>, grid, dim3(64), st, a);
+        else return hipErrorInvalidValue;
+    } else if (uni) {
+        launch(conv_lat<T, false, true, 1>, grid, dim3(64), st, a);
+    } else {
+        launch(conv_lat<T, false, false, 1>, grid, dim3(64), st, a);
+    }
+    return hipGetLastError();
+}
+
 hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
     if (a0.nimg <= 0) return hipSuccess;
     ConvArgs a = a0;
@@ -2228,6 +2535,8 @@ hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
     a.ksplit = a.part && !a.pool && c >= D_64x32 ? conv_splitk(dt, a) : 1;
     if (a.ksplit > 1 && (long)a.ksplit * a.nimg * a.P * a.Q * a.N * 4 >= (1l << 33))
         return hipErrorInvalidValue;
+    if (lat_ok(dt, a, c))
+        return dt == DT_F32 ? run_lat<float>(a, false, st) : run_lat<_Float16>(a, img_cfg(c), st);
     switch (c) {
     case F32_N16: return run_conv<float, 4, 128, 16, 4, 1>(a, st);
     case F32_N32: return run_conv<float, 4, 128, 32, 4, 1>(a, st);
