@@ -1302,25 +1302,35 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
 // fp16 into an LDS copy of the tile, and writes whole NHWC rows (or the
 // pooled rows, with maxpool_fixed's comparisons) with 16-byte stores.
 // ---------------------------------------------------------------------------
-template <int BN> struct PpWaves {
-    static constexpr int WM = BN == 256 ? 2 : 4;     // waves along pixels
-    static constexpr int WN = 8 / WM;                // waves along channels
-};
+// acc += w x on the matrix core, accumulating in place in AGPRs.  With more
+// than about 200 accumulator registers the compiler's own form of the
+// instruction gets separate source and destination registers and a copy per
+// MFMA (244 in conv_pp's loop of 112 MFMAs).  The compiler does not see an
+// MFMA here: mfma_done() must come between the last one and the first
+// ordinary use of an accumulator.
+__device__ __forceinline__ void mfma16_acc(f32x4 &acc, f16x8 w, f16x8 x) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+__device__ __forceinline__ void mfma_done() {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+}
 
 template <int BN, int BM, int TW, bool POOL>
-__global__ __launch_bounds__(512, 2) void conv_pp(ConvArgs a) {
-    constexpr int WM = PpWaves<BN>::WM, WN = PpWaves<BN>::WN;
+__global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
+    constexpr int WM = 2, WN = 2;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int IM = TM / 16, IN = TN / 16;
     constexpr int TH = TW ? BM / TW : 1;
-    constexpr int STAGE = (BM + BN) * 128;
-    constexpr int AR = BM / 32;               // pixel DMA rounds (group 0)
-    constexpr int BR = BN / 2 / 32;              // channel DMA rounds per group
+    // LDS: three stages of pixel rows, two of channel rows
+    constexpr int XST = BM * 128, WST = BN * 128, WOFF = 3 * XST;
+    constexpr int AR = BM / 32, BR = BN / 32;    // pixel / channel DMAs per wave
     constexpr int EROW = BN + 8;                 // epilogue row, halves
-    constexpr int LDS_BYTES = 2 * STAGE > BM * EROW * 2 ? 2 * STAGE
-                                                          : BM * EROW * 2;
+    constexpr int MAIN = WOFF + 2 * WST;
+    constexpr int LDS_BYTES = MAIN > BM * EROW * 2 ? MAIN : BM * EROW * 2;
     static_assert(IN * WN * 16 == BN && IM * WM * 16 == BM, "tile");
-    static_assert(WN % 2 == 0 && BR >= 1, "channel halves");
+    static_assert(MAIN <= 163840 && BM % 32 == 0 && BN % 32 == 0, "stage");
     static_assert(!POOL || (TW >= 2 && TH % 2 == 0), "pool windows");
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
 
@@ -1361,19 +1371,19 @@ __global__ __launch_bounds__(512, 2) void conv_pp(ConvArgs a) {
         }
     };
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int grp = wave >> 2, wg = wave & 3;    // group, wave in group
-    const int wm = wave % WM, wn = wave / WM;    // group 0 owns wn < WN / 2
-    const int lrow = wg * 8 + (lane >> 3);       // row within a 32-row round
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;
+    const int lrow = wave * 8 + (lane >> 3);     // row within a 32-row round
     const int chunk = (lane & 7) ^ (lane >> 3);
     const int Ktot = a.R * a.S * a.Cs;
     const int nsteps = Ktot / 64;
     const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * a.Cs * 2);
     const Rsrc wr = make_rsrc(a.w, (long)a.N * Ktot * 2);
 
-    // DMA addressing.  Pixel rounds (group 0): byte offset of the tap-(0,0)
-    // input pixel and (ih0, iw0) packed as two 16-bit fields; rows past the
-    // map get ih0 = -16384 (every tap out of range, loads return zero).
+    // DMA addressing.  Pixel rounds: byte offset of the tap-(0,0) input
+    // pixel and (ih0, iw0) packed as two 16-bit fields; rows past the map
+    // get ih0 = -16384 (every tap out of range, loads return zero).
     int a_pix[AR], a_hw[AR];
 #pragma unroll
     for (int i = 0; i < AR; i++) {
@@ -1384,37 +1394,31 @@ __global__ __launch_bounds__(512, 2) void conv_pp(ConvArgs a) {
         a_hw[i] = (int)((unsigned)ih0 << 16) | (iw0 & 0xffff);
         a_pix[i] = ((img * a.H + ih0) * a.W + iw0) * a.Cs * 2 + chunk * 16;
     }
-    // channel rounds: this group's half of the channel rows
-    const int nrow0 = n0 + grp * (BN / 2) + lrow;
-    const int b_base = nrow0 * Ktot * 2 + chunk * 16;
+    // channel rounds (N is a multiple of BN): one lane offset, the round
+    // and the step in the scalar offset
+    const int b_base = (n0 + lrow) * Ktot * 2 + chunk * 16;
     const int b_round = 32 * Ktot * 2;
-    // the tap of the step a group issues next (wave-uniform: Cs % 64 == 0)
+    // the tap of the pixel rows issued next (wave-uniform: Cs % 64 == 0)
     int kc = 0, ks = 0, kr = 0;
-
-    auto issue = [&](int step, int stage) {
-        char *sb = lds + stage * STAGE;
-        if (grp == 0) {
-            const int tap = ((kr * a.W + ks) * a.Cs + kc) * 2;
-#pragma unroll
-            for (int i = 0; i < AR; i++) {
-                const int ih = (a_hw[i] >> 16) + kr;
-                const int iw = (int)(short)(a_hw[i] & 0xffff) + ks;
-                const bool ok = (unsigned)ih < (unsigned)a.H &&
-                                (unsigned)iw < (unsigned)a.W;
-                dma16(xr, sb + (i * 32 + wg * 8) * 128, ok ? a_pix[i] + tap : OOB);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < BR; i++) {
-            const bool ok = nrow0 + i * 32 < a.N;
-            dma16(wr, sb + (BM + grp * (BN / 2) + i * 32 + wg * 8) * 128,
-                  ok ? b_base + i * b_round + step * 128 : OOB);
-        }
-        kc += 64;                     // k = (r, s, c): channels fastest
-        if (kc == a.Cs) {
-            kc = 0;
-            if (++ks == a.S) { ks = 0; ++kr; }
-        }
+    auto issue_x = [&](int i, int st) {
+        const int ih = (a_hw[i] >> 16) + kr, iw = (int)(short)(a_hw[i] & 0xffff) + ks;
+        const bool ok = (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
+        dma16(xr, lds + st + (i * 32 + wave * 8) * 128,
+              ok ? a_pix[i] + ((kr * a.W + ks) * a.Cs + kc) * 2 : OOB);
+    };
+    auto issue_w = [&](int i, int step, int st) {
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(
+            wr, (LdsPtr)(lds + st + (i * 32 + wave * 8) * 128), 16, b_base,
+            i * b_round + step * 128, 0, 0);
+    };
+    auto next_tap = [&]() {                      // k = (r, s, c): channels fastest
+        kc += 64;
+        const bool tap = kc == a.Cs;
+        kc = tap ? 0 : kc;
+        ks += tap;
+        const bool row = ks == a.S;
+        ks = row ? 0 : ks;
+        kr += row;
     };
 
     f32x4 acc[IN][IM];
@@ -1425,108 +1429,156 @@ __global__ __launch_bounds__(512, 2) void conv_pp(ConvArgs a) {
 
     const int fr = lane & 15, fg = lane >> 4;
     const int sw = fr & 7;
-    const int c0 = (fg ^ sw) * 16, c1 = ((4 + fg) ^ sw) * 16;
-    // one phase handles half a K step (32 halves: one 16x16x32 MFMA per
-    // fragment pair), which keeps the fragments of a phase (IN + IM
-    // registers of 16 bytes) next to the accumulators in 256 registers
-    f16x8 wf[IN], pf[IM];
-    auto load = [&](int stage, int kk) {
-        const char *la = lds + stage * STAGE + (wm * TM + fr) * 128;
-        const char *lb = lds + stage * STAGE + (BM + wn * TN + fr) * 128;
-        const int c = kk ? c1 : c0;
+    // fragment addresses in a stage, per half step, and the stages read next
+    int xa[2], wa[2], xst = 0, wst = WOFF;
 #pragma unroll
-        for (int i = 0; i < IN; i++)
-            wf[i] = *(const f16x8 *)(lb + i * 16 * 128 + c);
-#pragma unroll
-        for (int j = 0; j < IM; j++)
-            pf[j] = *(const f16x8 *)(la + j * 16 * 128 + c);
-    };
-    auto mfma = [&]() {
-#pragma unroll
-        for (int i = 0; i < IN; i++)
-#pragma unroll
-            for (int j = 0; j < IM; j++)
-                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
-                    wf[i], pf[j], acc[i][j], 0, 0, 0);
-    };
-    auto bar = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        asm volatile("" ::: "memory");
-    };
-    auto wait_lds = [&]() {
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_waitcnt(0xc07f);      // lgkmcnt 0
-        __builtin_amdgcn_sched_barrier(0);
-    };
-
-    // Half step h = 2 j + kk.  A group's DMA of step j + 1 goes out with
-    // its reads of half step 2 j and is awaited before its reads of 2 j + 2
-    // (four phases later); the stage it overwrites was last read in the
-    // phases of step j - 1.
-    issue(0, 0);
-    const int nh = 2 * nsteps;
-    for (int h = 0; h <= nh; h++) {
-        const int j = h >> 1, kk = h & 1;
-        // phase X: group 0 reads half step h, group 1 runs h - 1
-        if (grp == 0 && kk == 0) wait_vmcnt<0>();
-        bar();
-        if (grp == 0) {
-            if (h < nh) {
-                load(j & 1, kk);
-                if (kk == 0 && j + 1 < nsteps) issue(j + 1, (j + 1) & 1);
-                wait_lds();
-            }
-        } else {
-            if (h > 0) mfma();
-            if (kk == 0) wait_vmcnt<0>();
-        }
-        bar();
-        // phase Y: group 0 runs half step h, group 1 reads it
-        if (grp == 0) {
-            if (h < nh) mfma();
-        } else {
-            if (h < nh) {
-                load(j & 1, kk);
-                if (kk == 0 && j + 1 < nsteps) issue(j + 1, (j + 1) & 1);
-                wait_lds();
-            }
-        }
+    for (int kk = 0; kk < 2; kk++) {
+        const int c = ((kk * 4 + fg) ^ sw) * 16;
+        xa[kk] = (wm * TM + fr) * 128 + c;
+        wa[kk] = (wn * TN + fr) * 128 + c;
     }
-    bar();
+    f16x8 wf[2][IN], pf[2][IM];
+    auto read = [&](int kk, int i) {             // fragment i of half step kk
+        if (i < IM) pf[kk][i] = *(const f16x8 *)(lds + (xst + xa[kk]) + i * 16 * 128);
+        else wf[kk][i - IM] = *(const f16x8 *)(lds + (wst + wa[kk]) + (i - IM) * 16 * 128);
+    };
+    auto fence = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // The MFMAs of half step kk, in IN groups.  RD: the fragments of the
+    // next half step are read meanwhile; DM: and rows of step + 2 go out, the
+    // pixel rows during half 0, the channel rows during half 1: one or two
+    // DMAs a group, because a wave's MFMAs wait behind a DMA that finds the
+    // address unit busy (16 clocks for each of the four waves' DMAs)
+    constexpr int RPG = (IM + IN + IN - 1) / IN;
+    constexpr int XPG = (AR + IN - 1) / IN, WPG = (BR + IN - 1) / IN;
+    auto half = [&](auto kkc, auto rd, auto dm, int step, int to) {
+        constexpr int kk = decltype(kkc)::value;
+#pragma unroll
+        for (int i = 0; i < IN; i++) {
+            if constexpr (decltype(rd)::value)
+#pragma unroll
+                for (int r = i * RPG; r < (i + 1) * RPG; r++)
+                    if (r < IM + IN) read(kk ^ 1, r);
+            if constexpr (decltype(dm)::value && kk == 0)
+#pragma unroll
+                for (int r = i * XPG; r < (i + 1) * XPG; r++)
+                    if (r < AR) issue_x(r, to);
+            if constexpr (decltype(dm)::value && kk == 1)
+#pragma unroll
+                for (int r = i * WPG; r < (i + 1) * WPG; r++)
+                    if (r < BR) issue_w(r, step, to);
+#pragma unroll
+            for (int j = 0; j < IM; j++) mfma16_acc(acc[i][j], wf[kk][i], pf[kk][j]);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    typedef std::integral_constant<int, 0> H0;
+    typedef std::integral_constant<int, 1> H1;
+    typedef std::true_type Y;
+    typedef std::false_type N_;
+
+    // Steps 0 and 1 go out, then per step j: half 0 runs while half 1's
+    // fragments arrive and the pixel rows of step j + 2 go out (into the
+    // stage of step j - 1); once every wave has its fragments (barrier)
+    // step j's channel stage is free for step j + 2, and step j + 1 (waited
+    // for before the barrier; only the pixel rows just sent may be in
+    // flight) can be read: half 1 runs while its first half arrives.
+    auto all_x = [&](int st) {
+#pragma unroll
+        for (int i = 0; i < AR; i++) issue_x(i, st);
+        next_tap();
+    };
+    auto all_w = [&](int step, int st) {
+#pragma unroll
+        for (int i = 0; i < BR; i++) issue_w(i, step, st);
+    };
+    auto sync = [&](auto last) {                 // vmcnt, lgkmcnt 0, barrier
+        fence();
+        if constexpr (decltype(last)::value) wait_vmcnt<0>();
+        else wait_vmcnt<AR>();
+        __builtin_amdgcn_s_barrier();
+        fence();
+    };
+    all_x(0);
+    all_w(0, WOFF);
+    all_x(XST);
+    all_w(1, WOFF + WST);
+    fence();
+    wait_vmcnt<AR + BR>();
+    __builtin_amdgcn_s_barrier();
+    fence();
+#pragma unroll
+    for (int r = 0; r < IM + IN; r++) read(0, r);
+    auto next_stage = [&](int st) { return st == 2 * XST ? 0 : st + XST; };
+    auto advance = [&]() {                       // to the stages of the next step
+        xst = next_stage(xst);
+        wst = 2 * WOFF + WST - wst;
+    };
+    for (int j = 0; j + 2 < nsteps; j++) {
+        const int wto = wst;
+        half(H0(), Y(), Y(), j + 2, next_stage(next_stage(xst)));
+        next_tap();
+        sync(N_());
+        advance();
+        half(H1(), Y(), Y(), j + 2, wto);
+    }
+    half(H0(), Y(), N_(), 0, 0);                 // step nsteps - 2
+    sync(Y());
+    advance();
+    half(H1(), Y(), N_(), 0, 0);
+    half(H0(), Y(), N_(), 0, 0);                 // the last step
+    half(H1(), N_(), N_(), 0, 0);
+    mfma_done();
+    fence();
+    __builtin_amdgcn_s_waitcnt(0xc07f);
+    __builtin_amdgcn_s_barrier();
+    fence();
 
     // Epilogue: y = relu(acc * scale + shift (+ residual)) rounded to fp16
     // into an LDS copy of the tile (rows of EROW halves), then whole rows
-    // (or pooled rows) to HBM.
+    // (or pooled rows) to HBM.  One workgroup a CU: nothing runs under it,
+    // so no division by the map's sizes here (tile rows of a raster tile are
+    // consecutive output pixels) and the copy loop keeps several rows in
+    // flight (with a division per row and one row at a time it took about
+    // 12 us a tile).
     _Float16 *ep = (_Float16 *)lds;
     const _Float16 *res = (const _Float16 *)a.res;
+    // output pixel of tile row r as a row of y (-1: past the map / batch)
+    auto out_row = [&](int r) -> int {
+        if constexpr (TW > 0) {
+            const int p = p0 + r / TW, q = q0 + r % TW;
+            return p < a.P && q < a.Q ? (img0 * a.P + p) * a.Q + q : -1;
+        } else {
+            return m0 + r < M ? m0 + r : -1;
+        }
+    };
+    // (no branch per value: the comparison against -inf keeps every value)
+    const float lim = a.relu ? 0.f : -__builtin_inff();
 #pragma unroll
     for (int i = 0; i < IN; i++) {
         const int nl = wn * TN + i * 16 + fg * 4;
-        const bool nok = n0 + nl < a.N;
-        const f32x4 sc = nok ? *(const f32x4 *)(a.scale + n0 + nl) : (f32x4)(0.f);
-        const f32x4 sh = nok ? *(const f32x4 *)(a.shift + n0 + nl) : (f32x4)(0.f);
+        const f32x4 sc = *(const f32x4 *)(a.scale + n0 + nl);
+        const f32x4 sh = *(const f32x4 *)(a.shift + n0 + nl);
+        f32x4 v[IM];
+#pragma unroll
+        for (int j = 0; j < IM; j++) v[j] = acc[i][j] * sc + sh;
+        if (res) {
+#pragma unroll
+            for (int j = 0; j < IM; j++) {
+                const int o = out_row(wm * TM + j * 16 + fr);
+                const f16x4 rv = *(const f16x4 *)(res + (size_t)(o < 0 ? 0 : o) * a.N + n0 + nl);
+#pragma unroll
+                for (int e = 0; e < 4; e++) v[j][e] += (float)rv[e];
+            }
+        }
 #pragma unroll
         for (int j = 0; j < IM; j++) {
-            const int r = wm * TM + j * 16 + fr;
-            f32x4 v = acc[i][j] * sc + sh;
-            if (res) {
-                int img, p, q;
-                if (nok && pixel(r, img, p, q)) {
-                    const f16x4 rv = *(const f16x4 *)(
-                        res + ((size_t)(img * a.P + p) * a.Q + q) * a.N + n0 + nl);
+            f16x4 h;
 #pragma unroll
-                    for (int e = 0; e < 4; e++) v[e] += (float)rv[e];
-                }
-            }
-            if (a.relu) {
-#pragma unroll
-                for (int e = 0; e < 4; e++) v[e] = relu_nan(v[e]);
-            }
-            *(f16x4 *)(ep + r * EROW + nl) =
-                (f16x4){(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+            for (int e = 0; e < 4; e++) h[e] = (_Float16)(v[j][e] < lim ? 0.f : v[j][e]);
+            *(f16x4 *)(ep + (wm * TM + j * 16 + fr) * EROW + nl) = h;
         }
     }
     asm volatile("" ::: "memory");
@@ -1536,22 +1588,26 @@ __global__ __launch_bounds__(512, 2) void conv_pp(ConvArgs a) {
     _Float16 *y = (_Float16 *)a.y;
     constexpr int CPR = BN / 8;                  // 8-channel pieces per row
     if constexpr (!POOL) {
-        for (int idx = tid; idx < BM * CPR; idx += 512) {
-            const int r = idx / CPR, c = idx % CPR;
-            const int n = n0 + c * 8;
-            int img, p, q;
-            if (n >= a.N || !pixel(r, img, p, q)) continue;
-            const _Float16 *e = ep + r * EROW + c * 8;
-            _Float16 *o = y + ((size_t)(img * a.P + p) * a.Q + q) * a.N + n;
-            if (n + 8 <= a.N) *(f16x8 *)o = *(const f16x8 *)e;
-            else *(f16x4 *)o = *(const f16x4 *)e;
+        constexpr int RPT = 256 / CPR, IT = BM / RPT, U = 7;   // rows a pass, passes
+        static_assert(256 % CPR == 0 && BM % RPT == 0 && IT % U == 0, "copy");
+        const int c = tid % CPR, r0 = tid / CPR;
+        for (int k = 0; k < IT; k += U) {
+            f16x8 v[U];
+#pragma unroll
+            for (int u = 0; u < U; u++)
+                v[u] = *(const f16x8 *)(ep + (r0 + (k + u) * RPT) * EROW + c * 8);
+#pragma unroll
+            for (int u = 0; u < U; u++) {
+                const int o = out_row(r0 + (k + u) * RPT);
+                if (o >= 0) *(f16x8 *)(y + (size_t)o * a.N + n0 + c * 8) = v[u];
+            }
         }
     } else {
         // 2x2 stride-2 max pool of the stored (fp16) values, window order
         // and NaN rule of maxpool_fixed
         const int PP = a.P / 2, QP = a.Q / 2;
         constexpr int PW = TW / 2;
-        for (int idx = tid; idx < (BM / 4) * CPR; idx += 512) {
+        for (int idx = tid; idx < (BM / 4) * CPR; idx += 256) {
             const int pr = idx / CPR, c = idx % CPR;
             const int n = n0 + c * 8;
             const int pp = p0 / 2 + pr / PW, pq = q0 / 2 + pr % PW;
@@ -1589,7 +1645,7 @@ static hipError_t run_pp(const ConvArgs &a, hipStream_t st) {
     long mt = TW ? (long)a.nimg * ((a.P + TH - 1) / TH) * ((a.Q + TW - 1) / TW)
                  : ((long)a.nimg * a.P * a.Q + BM - 1) / BM;
     const long tiles = mt * ((a.N + BN - 1) / BN);
-    launch(conv_pp<BN, BM, TW, POOL>, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(512), st, a);
+    launch(conv_pp<BN, BM, TW, POOL>, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), st, a);
     return hipGetLastError();
 }
 
