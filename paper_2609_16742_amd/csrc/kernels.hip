@@ -351,10 +351,11 @@ template <int N> __device__ __forceinline__ void wait_vmcnt() {
     __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | ((N >> 4) << 14));
 }
 typedef __attribute__((address_space(3))) void *LdsPtr;
-// 16 bytes per lane from buffer offset `voff` into LDS at lds + 16 * lane
-// (`lds` must be the same for the whole wave)
-__device__ __forceinline__ void dma16(Rsrc r, void *lds, int voff) {
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LdsPtr)lds, 16, voff, 0, 0, 0);
+// 16 bytes per lane from buffer offset `voff` + `soff` into LDS at lds + 16 *
+// lane (`lds` and `soff` must be the same for the whole wave; `soff` keeps
+// an in-range `voff` inside the buffer)
+__device__ __forceinline__ void dma16(Rsrc r, void *lds, int voff, int soff = 0) {
+    __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LdsPtr)lds, 16, voff, soff, 0, 0);
 }
 
 // The epilogue of the LDS-staged implicit-GEMM convolution (conv_dma), run
@@ -835,14 +836,19 @@ __global__ __launch_bounds__(256) void splitk_reduce(ConvArgs a) {
 // are read from one LDS copy of the image (with its zero border) instead
 // of once per tap and per pixel tile, and the filters are read once per
 // image instead of once per pixel tile (the implicit GEMM re-reads both
-// from L2 and, at 49 pixels per image, needs split-K to fill the GPU).  The 4 waves each
-// own 16 output channels and every pixel tile of the image; a wave streams
-// its own filter rows through a private LDS ring (no barrier), and the
-// 64-channel input planes go through two shared halo buffers with one
-// workgroup barrier per plane (plane c + 1 loads while plane c's 9 taps
-// run).  The k loop runs plane by plane, taps inside a plane, so the sums
-// are taken in another order than conv_dma's; the epilogue (and the fused
-// 2x2 pool) is conv_dma's.
+// from L2 and, at 49 pixels per image, needs split-K to fill the GPU).  The
+// 64-channel input planes go through two halo buffers, the filter rows
+// through a ring of four steps.  Four waves, two along the channels and two
+// along the pixels: on a 14x14 map 9 fragment reads feed a wave's 14 MFMAs
+// of a half step (with four waves of 16 channels and every pixel they were
+// 14 per 13, and the LDS read port, 900 clocks a step against 420 of MFMA,
+// was what bounded the kernel).  The next half step's fragments are read
+// under the current one's MFMAs, with one barrier a step between the two
+// halves.  Measured, four 16-channel waves -> this: 14x14x256 at batch 64
+// 32.2 -> 22.7 us, 14x14x512 at batch 32 54.5 -> 38.7, 7x7x512 at batch 64
+// 27.3 -> 25.3, 14x14x256 -> 7x7x512 24.2 -> 21.8.  The k loop runs plane by
+// plane, taps inside a plane, so the sums are taken in another order than
+// conv_dma's; the epilogue (and the fused 2x2 pool) is conv_dma's.
 // ---------------------------------------------------------------------------
 // conv_img's XCD split: the 8 XCDs form an XA x (8 / XA) grid, XCD (xa,
 // xb) running channel groups xa, xa + XA, ... of the images of slice xb,
@@ -861,19 +867,22 @@ __host__ __device__ inline int img_xa(const ConvArgs &a) {
     return xa;
 }
 
+// Halo DMAs a wave sends at tap t, two a tap until all hd are out.
+constexpr int img_halos(int hd, int t) {
+    return t < 0 || 2 * t >= hd ? 0 : hd - 2 * t > 2 ? 2 : hd - 2 * t;
+}
+
 template <int TW, bool POOL, int ST = 1>
 __global__ __launch_bounds__(256) void conv_img(ConvArgs a) {
-    constexpr int BN = 64, WM = 1, WN = 4, NSB = 4, GR = 32;
-    constexpr int BM = (TW * TW + 15) / 16 * 16, IM = BM / 16;
+    constexpr int BN = 64, WM = 2, WN = 2, NSW = 4, GR = 32;
+    constexpr int PT = (TW * TW + 15) / 16, IM = (PT + 1) / 2, IN = 2, BM = WM * IM * 16;
     // halo side: the input rows / columns -1 .. (TW - 1) ST + 1
     constexpr int HTW = (TW - 1) * ST + 3, HR = (HTW * HTW + GR - 1) / GR * GR;
     constexpr int HD = HR / GR;                           // halo DMAs per plane
-    constexpr int HBYTES = HR * 128;
-    constexpr int WRING = NSB * 16 * 128;                 // a wave's filter ring
+    constexpr int HBYTES = HR * 128, WST = BN * 128;
     constexpr int EROW = BN + 4;
-    constexpr int MAIN = 2 * HBYTES + 4 * WRING;
+    constexpr int MAIN = 2 * HBYTES + NSW * WST;
     constexpr int LDS_BYTES = MAIN > BM * EROW * 4 ? MAIN : BM * EROW * 4;
-    static_assert(2 * (NSB - 1) + HD < 64, "vmcnt");
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
 
     const int nct = a.N / BN, xa_n = img_xa(a), xb_n = 8 / xa_n;
@@ -882,115 +891,149 @@ __global__ __launch_bounds__(256) void conv_img(ConvArgs a) {
     const int il = idx / cpa, img = xcd / xa_n * ipb + il;
     if (il >= ipb || img >= a.nimg) return;
     const int n0 = (idx % cpa * xa_n + xcd % xa_n) * BN;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % WM, wn = wave / WM;
     const int lrow = wave * 8 + (lane >> 3);
-    const int chunk = (lane & 7) ^ (lane >> 3);
-    const int planes = a.Cs / 64, nsteps = 9 * planes, Ktot = 9 * a.Cs;
+    const int planes = a.Cs / 64, Ktot = 9 * a.Cs;
     const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * a.Cs * 2);
     const Rsrc wr = make_rsrc(a.w, (long)a.N * Ktot * 2);
-    char *ring = lds + 2 * HBYTES + wave * WRING;
-    // the wave's 16 filter rows, 8 per DMA instruction: row n0 + 16 wave +
-    // 8 i + (lane >> 3), its chunk swizzled by the row's low bits
-    const int b_row0 = (n0 + wave * 16 + (lane >> 3)) * Ktot * 2 + chunk * 16;
 
-    auto issue_b = [&](int step) {
-        const int k0 = (step % 9) * a.Cs + (step / 9) * 64;
-        char *sl = ring + (step % NSB) * 2048;
+    // Filter rows: row lrow + 32 i of the 64, its chunk swizzled by the
+    // row's low bits; (plane, tap) in the scalar offset.  Past the last
+    // plane the DMAs read zeros (and keep the wait counts the same).
+    const int w_row = (n0 + lrow) * Ktot * 2 + ((lane & 7) ^ (lane >> 3)) * 16;
+    auto issue_w = [&](int plane, int tap, int slot) {
+        const bool ok = plane < planes;
 #pragma unroll
         for (int i = 0; i < 2; i++)
-            dma16(wr, sl + i * 1024,
-                  step < nsteps ? b_row0 + i * 8 * Ktot * 2 + k0 * 2 : OOB);
+            dma16(wr, lds + 2 * HBYTES + slot * WST + (i * 32 + wave * 8) * 128,
+                  ok ? w_row : OOB, ok ? i * 32 * Ktot * 2 + (tap * a.Cs + plane * 64) * 2 : 0);
     };
     // Halo rows are swizzled by hkey(rh) = (hy / ST) TW + hx / ST (mod 8)
     // of the halo pixel (hy, hx): for any tap, 8 consecutive output pixels
     // (wrapping from one output row to the next) read halo rows with 8
     // distinct keys, so their 16-byte reads hit distinct bank groups (a key
     // of the row number alone repeats where a row wraps).
-    auto issue_h = [&](int plane) {
+    int h_off[HD];
 #pragma unroll
-        for (int i = 0; i < HD; i++) {
-            const int rh = i * GR + lrow;
-            const int hy = rh / HTW, hx = rh % HTW, ih = hy - 1, iw = hx - 1;
-            const int hch = (lane & 7) ^ ((hy / ST * TW + hx / ST) & 7);
-            const bool ok = plane < planes && rh < HTW * HTW &&
-                            (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-            dma16(xr, lds + (plane & 1) * HBYTES + (i * GR + wave * 8) * 128,
-                  ok ? (((img * a.H + ih) * a.W + iw) * a.Cs + plane * 64) * 2 + hch * 16
-                     : OOB);
-        }
+    for (int i = 0; i < HD; i++) {
+        const int rh = i * GR + lrow;
+        const int hy = rh / HTW, hx = rh % HTW, ih = hy - 1, iw = hx - 1;
+        const int hch = (lane & 7) ^ ((hy / ST * TW + hx / ST) & 7);
+        const bool ok = rh < HTW * HTW && (unsigned)ih < (unsigned)a.H &&
+                        (unsigned)iw < (unsigned)a.W;
+        h_off[i] = ok ? ((img * a.H + ih) * a.W + iw) * a.Cs * 2 + hch * 16 : OOB;
+    }
+    auto issue_h = [&](int i, int plane) {
+        const bool ok = plane < planes;
+        dma16(xr, lds + (plane & 1) * HBYTES + (i * GR + wave * 8) * 128,
+              ok ? h_off[i] : OOB, ok ? plane * 128 : 0);
     };
 
     const int fr = lane & 15, fg = lane >> 4;
-    // the lane's output pixel rr in each pixel tile: the halo row of its
-    // tap (0, 0) times 8, plus rr mod 8, whose sum with a tap's key
-    // offset is the key of the halo row the tap reads (tile rows past the
-    // map take pixel 0; their results are not stored)
-    int hbase[IM];
+    // the lane's output pixel rr in each pixel tile: the byte offset of its
+    // tap-(0, 0) halo row, and rr's key times 16, whose sum with a tap's key
+    // is the key of the halo row the tap reads (tile rows past the map take
+    // pixel 0; their results are not stored)
+    int hrow[IM], hkey[IM];
 #pragma unroll
     for (int j = 0; j < IM; j++) {
-        const int r = j * 16 + fr, rr = r < TW * TW ? r : 0;
-        hbase[j] = (rr / TW * ST * HTW + rr % TW * ST) * 8 + (rr & 7);
+        const int r = (wm * IM + j) * 16 + fr, rr = r < TW * TW ? r : 0;
+        hrow[j] = (rr / TW * ST * HTW + rr % TW * ST) * 128;
+        hkey[j] = (rr & 7) * 16;
     }
-    f32x4 acc[1][IM];
+    const int wa = 2 * HBYTES + (wn * 32 + fr) * 128 + (fg ^ (fr & 7)) * 16;
+    f32x4 acc[IN][IM];
 #pragma unroll
-    for (int j = 0; j < IM; j++) acc[0][j] = (f32x4)(0.f);
-    const int sw = fr & 7;
+    for (int i = 0; i < IN; i++)
+#pragma unroll
+        for (int j = 0; j < IM; j++) acc[i][j] = (f32x4)(0.f);
+    f16x8 wf[2][IN], pf[2][IM];
+    int xa[IM];                                  // chunk fg of the tap's halo rows
+    auto set_tap = [&](int t) {
+        const int tkey = ((t / 3 / ST * TW + t % 3 / ST) & 7) * 16;
+#pragma unroll
+        for (int j = 0; j < IM; j++) xa[j] = hrow[j] + (((hkey[j] + tkey) & 0x70) ^ (fg * 16));
+    };
+    auto fence = [&]() {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // fragment r of half step kk of a step: tap t, filter slot, halo buffer
+    auto read = [&](int kk, int r, int t, int slot, int hb) {
+        if (r < IN)
+            wf[kk][r] = *(const f16x8 *)(lds + slot * WST + (wa ^ (kk * 64)) + r * 16 * 128);
+        else
+            pf[kk][r - IN] = *(const f16x8 *)(lds + hb + (xa[r - IN] ^ (kk * 64)) +
+                                              (t / 3 * HTW + t % 3) * 128);
+    };
+    constexpr int RPG = (IM + IN + 1) / 2;
+    auto mfmas = [&](int kk, int i) {
+#pragma unroll
+        for (int j = 0; j < IM; j++)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[kk][i], pf[kk][j], acc[i][j],
+                                                              0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
 
-    // prologue: plane 0's halo, then the first NSB - 1 steps' filter rows
-    issue_h(0);
+    // Step s = (plane c, tap t).  Half 0 runs while half 1's fragments
+    // arrive; once every wave has them (barrier), slot s % 4 is free for the
+    // filter rows of step s + 4 and, after a plane's last step, its halo
+    // buffer for plane c + 2 (two DMAs a tap from tap 0 on); half 1 runs
+    // while the first half of step s + 1 arrives.
 #pragma unroll
-    for (int s = 0; s < NSB - 1; s++) issue_b(s);
-    for (int c = 0; c < planes; c++) {
-        // plane c's halo has landed once only the filter-row DMAs issued
-        // after it are in flight (NSB - 1 steps' worth); the barrier then
-        // publishes every wave's share and ends all reads of plane c - 1,
-        // whose buffer plane c + 1 now takes
-        wait_vmcnt<2 * (NSB - 1)>();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        issue_h(c + 1);                       // (past the last plane: no-op DMAs)
-        const char *lh = lds + (c & 1) * HBYTES;
-        for (int tp = 0; tp < 9; tp++) {
-            const int s = 9 * c + tp;
-            // step s's filter rows: younger are the NSB - 2 later steps'
-            // rows and, for the first NSB - 1 taps of the plane, the next
-            // plane's halo (issued after those rows)
-            if (tp < NSB - 1) wait_vmcnt<2 * (NSB - 2) + HD>();
-            else wait_vmcnt<2 * (NSB - 2)>();
-            const char *lb = ring + (s % NSB) * 2048 + fr * 128;
-            const int off = tp / 3 * HTW + tp % 3;
-            const int tkey = tp / 3 / ST * TW + tp % 3 / ST;
-            f16x8 wf[2], pf[2][IM];
+    for (int i = 0; i < HD; i++) issue_h(i, 0);
 #pragma unroll
-            for (int kk = 0; kk < 2; kk++) {
-                const int g = kk * 4 + fg;
-                wf[kk] = *(const f16x8 *)(lb + ((g ^ sw) * 16));
-#pragma unroll
-                for (int j = 0; j < IM; j++) {
-                    const int rh = (hbase[j] >> 3) + off;
-                    const int key = (hbase[j] + tkey) & 7;
-                    pf[kk][j] = *(const f16x8 *)(lh + rh * 128 + ((g ^ key) * 16));
-                }
-            }
-            // the slot read above is refilled NSB - 1 steps later: its
-            // reads must have returned first
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_s_waitcnt(0xc07f);       // lgkmcnt 0
-            asm volatile("" ::: "memory");
-            issue_b(s + NSB - 1);
-#pragma unroll
-            for (int kk = 0; kk < 2; kk++)
-#pragma unroll
-                for (int j = 0; j < IM; j++)
-                    acc[0][j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(wf[kk], pf[kk][j],
-                                                                      acc[0][j], 0, 0, 0);
-        }
-    }
-    wait_vmcnt<0>();
-    asm volatile("" ::: "memory");
+    for (int s = 0; s < NSW; s++) issue_w(0, s, s);
+    fence();
+    wait_vmcnt<2 * (NSW - 1)>();
     __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
+    fence();
+    set_tap(0);
+#pragma unroll
+    for (int r = 0; r < IM + IN; r++) read(0, r, 0, 0, 0);
+    for (int c = 0; c < planes; c++) {
+        const int hb = (c & 1) * HBYTES, hn = HBYTES - hb;
+        auto step = [&](auto tc) {
+            constexpr int t = decltype(tc)::value, tn = t == 8 ? 0 : t + 1;
+            const int slot = (c + t) & 3;
+#pragma unroll
+            for (int i = 0; i < IN; i++) {
+#pragma unroll
+                for (int r = i * RPG; r < (i + 1) * RPG && r < IM + IN; r++)
+                    read(1, r, t, slot, hb);
+                mfmas(0, i);
+            }
+            // younger than step s + 1's filter rows: those of the next two
+            // steps and the halo DMAs sent between them
+            fence();
+            wait_vmcnt<2 * (NSW - 2) + img_halos(HD, t - 2) + img_halos(HD, t - 1)>();
+            __builtin_amdgcn_s_barrier();
+            fence();
+            set_tap(tn);
+#pragma unroll
+            for (int i = 0; i < IN; i++) {
+#pragma unroll
+                for (int r = i * RPG; r < (i + 1) * RPG && r < IM + IN; r++)
+                    read(0, r, tn, (slot + 1) & 3, t == 8 ? hn : hb);
+                if (i == 0)
+#pragma unroll
+                    for (int h = 2 * t; h < 2 * t + img_halos(HD, t); h++) issue_h(h, c + 1);
+                if (i == IN - 1) issue_w(t + NSW < 9 ? c : c + 1, (t + NSW) % 9, slot);
+                mfmas(1, i);
+            }
+        };
+        step(std::integral_constant<int, 0>());
+        step(std::integral_constant<int, 1>());
+        step(std::integral_constant<int, 2>());
+        step(std::integral_constant<int, 3>());
+        step(std::integral_constant<int, 4>());
+        step(std::integral_constant<int, 5>());
+        step(std::integral_constant<int, 6>());
+        step(std::integral_constant<int, 7>());
+        step(std::integral_constant<int, 8>());
+    }
     auto pixel = [&](int r, int &im, int &p, int &q) -> bool {
         im = img;
         p = r / TW;
@@ -1144,12 +1187,10 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
             const int so = plane * 128, sw = so + t * a.Cs * 2;
 #pragma unroll
             for (int i = 0; i < 2; i++)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (LdsPtr)(st + i * 1024), 16, wo[i],
-                                                         sw, 0, 0);
+                dma16(wr, st + i * 1024, wo[i], sw);
 #pragma unroll
             for (int i = 0; i < 2; i++)
-                __builtin_amdgcn_raw_ptr_buffer_load_lds(xr, (LdsPtr)(st + 2048 + i * 1024), 16,
-                                                         xo[t][i], so, 0, 0);
+                dma16(xr, st + 2048 + i * 1024, xo[t][i], so);
         };
         const int planes = a.Cs / 64;
 #pragma unroll
@@ -1279,24 +1320,30 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp16 implicit-GEMM convolution with a ping-pong wave schedule (dense
-// layers with at least 64 input channels).  Same GEMM view, operand roles,
-// LDS-DMA staging and row swizzle as conv_dma, for a 256-pixel x BN-channel
-// tile and K steps of 64 halves.  The 8 waves form two groups of four (one
-// wave of each group per SIMD) that alternate between two phases separated
-// by workgroup barriers: while one group reads the MFMA fragments of half
-// a K step from LDS into registers (and, every other phase, issues the DMA
-// of a later step), the other group runs that half step's MFMAs back to
-// back on fragments it already holds.  So the matrix core of every SIMD always has a wave with
-// nothing but MFMAs to issue, and LDS latency is hidden by the other
-// group instead of stalling the MFMA stream.  Group 0 stages the pixel rows
-// and the first half of the channel rows, group 1 the second half (each
-// group reads only its own half of the channels), each two phases ahead of
-// its first reader.  Per output, the MFMA sequence (k in order, two 16x16x32
-// MFMAs per 128-byte row) is conv_dma's, so results are bit-identical.
+// fp16 implicit-GEMM convolution for the widest layers (>= 64 input
+// channels, output channels in tiles of BN = 256).  Same GEMM view, operand
+// roles, LDS-DMA staging and row swizzle as conv_dma, for a BM-pixel x
+// BN-channel tile and K steps of 64 halves; one workgroup a CU, four waves
+// of BM / 2 pixels x 128 channels.  What bounds it on these layers is the
+// matrix core (and the power it draws) as long as nothing stalls its one
+// wave per SIMD, so:
+//  - large wave tiles: 15 fragment reads feed 56 MFMAs; with eight waves of
+//    64 channels they were 23 per 56, and the LDS, which also takes the
+//    DMAs, was the busier unit;
+//  - the fragments of the next half step are read, and the DMAs of a later
+//    step sent, between the MFMAs of the current half step (see `half`);
+//  - one barrier per K step, in the middle of it.
+// Per output, the MFMA sequence (k in order, two 16x16x32 MFMAs per 128-byte
+// row) is conv_dma's, so results are bit-identical.
+// Measured (batch 32, 3x3), eight waves alternating between reads and MFMAs
+// -> this: 56x56x256 132 -> 115 us, 28x28x512 123 -> 106 us (1.12 PFLOP/s),
+// 28x28 256 -> 512 70 -> 62 us.  With parts switched off in a copy, 28x28x512
+// takes 79 us for its MFMAs alone, 89 with the fragment reads, 95 with the
+// channel rows' and 104 with the pixel rows' DMAs as well; all-zero data
+// takes 10% less (the clock follows the power).
 //
-// Pixel tiles are TW == 0: 256 consecutive output pixels in NHWC order, or
-// TW > 0: a (256 / TW) x TW block of one image (for the fused 2x2 max
+// Pixel tiles are TW == 0: BM consecutive output pixels in NHWC order, or
+// TW > 0: a (BM / TW) x TW block of one image (for the fused 2x2 max
 // pool, POOL, whose windows must lie inside the tile).  The epilogue
 // applies scale / shift, the residual and ReLU in registers, rounds to
 // fp16 into an LDS copy of the tile, and writes whole NHWC rows (or the
@@ -1407,9 +1454,7 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
               ok ? a_pix[i] + ((kr * a.W + ks) * a.Cs + kc) * 2 : OOB);
     };
     auto issue_w = [&](int i, int step, int st) {
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(
-            wr, (LdsPtr)(lds + st + (i * 32 + wave * 8) * 128), 16, b_base,
-            i * b_round + step * 128, 0, 0);
+        dma16(wr, lds + st + (i * 32 + wave * 8) * 128, b_base, i * b_round + step * 128);
     };
     auto next_tap = [&]() {                      // k = (r, s, c): channels fastest
         kc += 64;
@@ -2460,8 +2505,10 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
 // 14x14x256 28.7 -> 13.4 (eight, 1664), fp32 56x56x64 19.2 -> 10.6.  Above
 // it the tiles that share rows win back what they lose in latency: 56x56x64
 // 11.6 = 11.6 at 3136 tiles, 28x28x72 -> 136 10.8 -> 14.7 at 3528, 14x14 96
-// -> 576 1x1 5.7 -> 9.3 at 3600.  conv_pw's layers, short in k, only up to
-// 1024: 96 -> 576 4.6 against 5.4 at 468 and 5.6 against 5.5 us at 1800.
+// -> 576 1x1 5.7 -> 9.3 at 3600.  Up to 1024 only: conv_pw's layers, short
+// in k (96 -> 576 5.4 -> 4.6 us at 468 tiles, 5.5 -> 5.6 at 1800), and the
+// 7x7 maps, whose own kernel has small tiles too (512 channels 15.8 -> 12.0
+// us at 800, 16.3 -> 22.4 at 1696).
 static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
     const int es = dt == DT_F32 ? 4 : 2;
     if (a.pool || (c < D_64x32 && c != PW_F16 && c != PP_256 && !img_cfg(c))) return false;
@@ -2469,7 +2516,8 @@ static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
         (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
         return false;
     const long M = (long)a.nimg * a.P * a.Q;
-    return (M + 15) / 16 * ((a.N + 15) / 16) <= (c == PW_F16 ? 1024 : 2048);
+    const bool few = c == PW_F16 || c == IMG_7 || c == IMG_7S2;
+    return (M + 15) / 16 * ((a.N + 15) / 16) <= (few ? 1024 : 2048);
 }
 
 const char *conv_kernel_name(int dt, const ConvArgs &a) {
