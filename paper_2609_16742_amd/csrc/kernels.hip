@@ -2364,7 +2364,7 @@ hipError_t launch_stem_pool(const ConvArgs &a, int PP, int QP, hipStream_t st) {
 enum ConvCfg {
     F32_N16, F32_N32, F32_N64,
     F16V4_N32, F16V4_N64, PW_F16, STEM_F16,
-    PP_256, PP_256_P8, PP_256_P16,
+    PP_256, PP_256_P8, PP_256_P16, PP_128,
     IMG_7, IMG_14,                              // conv_img on 7x7 / 14x14 maps
     IMG_7S2,                                    // conv_img, 14x14 -> 7x7 stride 2
     D_64x32, D_128x64, D_64x64, D_64x128, D_128x128, D_256x256,
@@ -2373,14 +2373,17 @@ enum ConvCfg {
 };
 
 // conv_pp on a layer: fp16 3x3 with whole 64-channel k steps, channel
-// tiles of 256, and enough 224-pixel tiles to fill the GPU (measured on
-// VGG-16's 56x56 and 28x28 layers: 5-9% faster than conv_dma's 256x256
-// tiles, whose 196 / 392 tiles leave a quarter of the last round idle;
-// slower on the 14x14 ones, 56 tiles)
-static bool pp_fits(const ConvArgs &a) {
+// tiles of bn, and enough 224-pixel tiles to fill three quarters of the
+// GPU's CUs, one each.  Measured against conv_dma, which takes the others:
+// bn = 256, 56x56x256 at batch 32 142 -> 115 us; bn = 128 (channel counts
+// that are no multiple of 256), 28x28x128 at batch 64 (224 tiles) 30.4 ->
+// 27.5 us, 56x56 64 -> 128 stride 2 (224) 19.1 -> 16.5, 28x28 192 -> 384 at
+// batch 56 (588) 89.4 -> 85.3; the halo tiles of layers with 64 input
+// channels come first (56x56 64 -> 128 61.7 us against 67.8).
+static bool pp_fits(const ConvArgs &a, int bn) {
     const long M = (long)a.nimg * a.P * a.Q;
-    return a.Cs % 64 == 0 && a.R == 3 && a.S == 3 && a.N % 256 == 0 &&
-           (M + 223) / 224 * (a.N / 256) >= 192 &&
+    return a.Cs % 64 == 0 && a.R == 3 && a.S == 3 && a.N % bn == 0 &&
+           (M + 223) / 224 * (a.N / bn) >= 192 &&
            (long)a.nimg * a.H * a.W * a.Cs * 2 < (1l << 31) &&
            (long)a.N * a.R * a.S * a.Cs * 2 < (1l << 31);
 }
@@ -2452,7 +2455,8 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         if (a.N <= 64) return a.pool ? H_128x64_P16 : H_128x64;
         if (!a.pool) return H_128x128;
     }
-    if (dt == DT_F16 && pp_fits(a)) {
+    if (dt == DT_F16 && !a.pool && a.N % 256 && pp_fits(a, 128)) return PP_128;
+    if (dt == DT_F16 && pp_fits(a, 256)) {
         if (!a.pool) return PP_256;
         // the tile width with fewer tiles (ties: 8)
         const long t8 = pool_tiles(a, 28, 8), t16 = pool_tiles(a, 14, 16);
@@ -2543,6 +2547,7 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
     case PW_F16: return pw_kernel_name(a);
     case STEM_F16: return stem_kernel_name(a);
     case PP_256: return "conv_pp<256, 224, 0, false>";
+    case PP_128: return "conv_pp<128, 224, 0, false>";
     case PP_256_P8: return "conv_pp<256, 224, 8, true>";
     case PP_256_P16: return "conv_pp<256, 224, 16, true>";
     case IMG_7: return "conv_img<7, false, 1>";
@@ -2650,6 +2655,7 @@ hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
     case PW_F16: return run_pw(a, st);
     case STEM_F16: return run_stem(a, st);
     case PP_256: return run_pp<256, 224, 0, false>(a, st);
+    case PP_128: return run_pp<128, 224, 0, false>(a, st);
     case PP_256_P8: return run_pp<256, 224, 8, true>(a, st);
     case PP_256_P16: return run_pp<256, 224, 16, true>(a, st);
     case IMG_7: return run_img<7, false>(a, st);

@@ -85,3 +85,52 @@ def test_small_batches_give_the_bits_of_large_ones(case):
     err = (ys.cpu().double().permute(0, 3, 1, 2) - ref.relu()).norm()
     # one rounding to 11 bits, or sums of K <= 4644 products in fp32
     assert err <= (2.0 ** -11 if dtype == "f16" else 1e-5) * ref.norm()
+
+
+# C, H, W, K, stride, residual, images large (conv_pp) / small (conv_dma)
+WIDE = [
+    # one 128-channel tile, ragged last pixel tile; two tiles; 9, 18, 27 steps
+    (64, 41, 35, 128, 2, True, 120, 90),
+    (128, 27, 29, 128, 1, True, 55, 12),
+    (192, 27, 29, 384, 1, False, 20, 8),
+    (256, 29, 27, 256, 1, True, 56, 10),
+]
+
+
+@pytest.mark.parametrize("case", WIDE)
+def test_wide_tiles_give_the_bits_of_small_ones(case):
+    import paper_2609_16742_amd as P
+    ctc = P.ctc
+    C, H, W, K, st, res, large, small = case
+    print("wide tiles", case, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(C + K)
+    p, q = ((d - 1) // st + 1 for d in (H, W))
+    d = ctc.layer_desc(C, K, 3, 3, st, 1, 1, 1, ctc.CTC_ROLE_SUM)
+
+    def rnd(*shape):
+        return torch.randn(shape, device="cuda", generator=g)
+
+    x, w = rnd(large, H, W, C).half(), (rnd(K, 3, 3, C) * 0.05).half()
+    scale, shift = rnd(K), rnd(K)
+    r = rnd(large, p, q, K).half() if res else None
+    x[1, H // 2, W // 2, 5] = float("inf")       # stays in its 3x3 windows
+
+    def run(n):
+        y = torch.full((n, p, q, K), float("nan"), device="cuda").half()
+        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x[:n], w, scale, shift,
+                               None if r is None else r[:n], 1, y)
+        return y
+
+    bn = 256 if K % 256 == 0 else 128
+    names = [ctc.ctc_conv2d_kernel_name(d, ctc.CTC_F16, n, H, W)
+             for n in (large, small)]
+    assert names[0] == "conv_pp<%d, 224, 0, false>" % bn
+    assert names[1].startswith("conv_dma<")
+    yl, ys = run(large), run(small)
+    torch.cuda.synchronize()
+    a, b = (t.cpu().numpy().view(np.uint16) for t in (yl[:small], ys))
+    nan = np.isnan(a.view(np.float16)) & np.isnan(b.view(np.float16))
+    assert np.array_equal(a[~nan], b[~nan]) and nan.sum() < 9 * K + 1
+    # every row past the small batch is written, and the inf stayed put
+    assert bool(torch.isfinite(yl[small:]).all())
