@@ -1349,20 +1349,25 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
 // fp16 into an LDS copy of the tile, and writes whole NHWC rows (or the
 // pooled rows, with maxpool_fixed's comparisons) with 16-byte stores.
 // ---------------------------------------------------------------------------
-// acc += w x on the matrix core, accumulating in place in AGPRs.  With more
-// than about 200 accumulator registers the compiler's own form of the
-// instruction gets separate source and destination registers and a copy per
-// MFMA (244 in conv_pp's loop of 112 MFMAs).  The compiler does not see an
-// MFMA here: mfma_done() must come between the last one and the first
-// ordinary use of an accumulator.
+// acc += w x on the matrix core, accumulating in place in AGPRs.  In a loop
+// like conv_pp's the compiler's own form of the instruction gets separate
+// source and destination registers and copies between them (232 in the loop
+// of 112 MFMAs, 12 in that of 8).  It does not see an MFMA here, so
+// it keeps none of the distances one needs before its result is read:
+// mfma_done() comes after the last one and mfma_result() on every
+// accumulator after that, before any other use, and nothing but MFMAs may
+// touch an AGPR between the first and the last of them (a test reads the
+// built kernels for it).
 __device__ __forceinline__ void mfma16_acc(f32x4 &acc, f16x8 w, f16x8 x) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
+// (12 wait states cover the 8 passes of a 16x16x32 MFMA)
 __device__ __forceinline__ void mfma_done() {
     __builtin_amdgcn_sched_barrier(0);
-    asm volatile("s_nop 15\n\ts_nop 15" ::: "memory");
+    asm volatile("s_nop 11" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
 }
+__device__ __forceinline__ void mfma_result(f32x4 &acc) { asm volatile("" : "+a"(acc)); }
 
 template <int BN, int BM, int TW, bool POOL>
 __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
@@ -1447,14 +1452,17 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     const int b_round = 32 * Ktot * 2;
     // the tap of the pixel rows issued next (wave-uniform: Cs % 64 == 0)
     int kc = 0, ks = 0, kr = 0;
-    auto issue_x = [&](int i, int st) {
+    auto issue_x = [&](int i, int st) {          // (no short circuits: a branch each)
         const int ih = (a_hw[i] >> 16) + kr, iw = (int)(short)(a_hw[i] & 0xffff) + ks;
-        const bool ok = (unsigned)ih < (unsigned)a.H && (unsigned)iw < (unsigned)a.W;
-        dma16(xr, lds + st + (i * 32 + wave * 8) * 128,
-              ok ? a_pix[i] + ((kr * a.W + ks) * a.Cs + kc) * 2 : OOB);
+        const bool ok = (kr < a.R) & ((unsigned)ih < (unsigned)a.H) &
+                        ((unsigned)iw < (unsigned)a.W);
+        const int off = a_pix[i] + ((kr * a.W + ks) * a.Cs + kc) * 2;
+        dma16(xr, lds + st + (i * 32 + wave * 8) * 128, ok ? off : OOB);
     };
     auto issue_w = [&](int i, int step, int st) {
-        dma16(wr, lds + st + (i * 32 + wave * 8) * 128, b_base, i * b_round + step * 128);
+        const bool ok = step < nsteps;           // past the layer: zeros
+        dma16(wr, lds + st + (i * 32 + wave * 8) * 128, ok ? b_base : OOB,
+              ok ? i * b_round + step * 128 : 0);
     };
     auto next_tap = [&]() {                      // k = (r, s, c): channels fastest
         kc += 64;
@@ -1498,31 +1506,27 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     // address unit busy (16 clocks for each of the four waves' DMAs)
     constexpr int RPG = (IM + IN + IN - 1) / IN;
     constexpr int XPG = (AR + IN - 1) / IN, WPG = (BR + IN - 1) / IN;
-    auto half = [&](auto kkc, auto rd, auto dm, int step, int to) {
+    auto half = [&](auto kkc, int step, int to) {
         constexpr int kk = decltype(kkc)::value;
 #pragma unroll
         for (int i = 0; i < IN; i++) {
-            if constexpr (decltype(rd)::value)
 #pragma unroll
-                for (int r = i * RPG; r < (i + 1) * RPG; r++)
-                    if (r < IM + IN) read(kk ^ 1, r);
-            if constexpr (decltype(dm)::value && kk == 0)
+            for (int r = i * RPG; r < (i + 1) * RPG; r++)
+                if (r < IM + IN) read(kk ^ 1, r);
 #pragma unroll
-                for (int r = i * XPG; r < (i + 1) * XPG; r++)
-                    if (r < AR) issue_x(r, to);
-            if constexpr (decltype(dm)::value && kk == 1)
+            for (int r = i * XPG; kk == 0 && r < (i + 1) * XPG; r++)
+                if (r < AR) issue_x(r, to);
 #pragma unroll
-                for (int r = i * WPG; r < (i + 1) * WPG; r++)
-                    if (r < BR) issue_w(r, step, to);
+            for (int r = i * WPG; kk == 1 && r < (i + 1) * WPG; r++)
+                if (r < BR) issue_w(r, step, to);
 #pragma unroll
-            for (int j = 0; j < IM; j++) mfma16_acc(acc[i][j], wf[kk][i], pf[kk][j]);
+            for (int j = 0; j < IM; j++)
+                mfma16_acc(acc[i][j], wf[kk][i], pf[kk][j]);
             __builtin_amdgcn_sched_barrier(0);
         }
     };
     typedef std::integral_constant<int, 0> H0;
     typedef std::integral_constant<int, 1> H1;
-    typedef std::true_type Y;
-    typedef std::false_type N_;
 
     // Steps 0 and 1 go out, then per step j: half 0 runs while half 1's
     // fragments arrive and the pixel rows of step j + 2 go out (into the
@@ -1539,10 +1543,9 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
 #pragma unroll
         for (int i = 0; i < BR; i++) issue_w(i, step, st);
     };
-    auto sync = [&](auto last) {                 // vmcnt, lgkmcnt 0, barrier
+    auto sync = [&]() {                          // vmcnt, lgkmcnt 0, barrier
         fence();
-        if constexpr (decltype(last)::value) wait_vmcnt<0>();
-        else wait_vmcnt<AR>();
+        wait_vmcnt<AR>();
         __builtin_amdgcn_s_barrier();
         fence();
     };
@@ -1561,23 +1564,23 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
         xst = next_stage(xst);
         wst = 2 * WOFF + WST - wst;
     };
-    for (int j = 0; j + 2 < nsteps; j++) {
+    // (the DMAs of the two steps past the end read zeros, so that the last
+    // steps need no code of their own)
+    for (int j = 0; j < nsteps; j++) {
         const int wto = wst;
-        half(H0(), Y(), Y(), j + 2, next_stage(next_stage(xst)));
-        next_tap();
-        sync(N_());
+        half(H0(), j + 2, next_stage(next_stage(xst)));
+        sync();
         advance();
-        half(H1(), Y(), Y(), j + 2, wto);
+        half(H1(), j + 2, wto);
+        next_tap();
+        mfma_done();                             // before any copy at the loop's end
     }
-    half(H0(), Y(), N_(), 0, 0);                 // step nsteps - 2
-    sync(Y());
-    advance();
-    half(H1(), Y(), N_(), 0, 0);
-    half(H0(), Y(), N_(), 0, 0);                 // the last step
-    half(H1(), N_(), N_(), 0, 0);
-    mfma_done();
+#pragma unroll
+    for (int i = 0; i < IN; i++)
+#pragma unroll
+        for (int j = 0; j < IM; j++) mfma_result(acc[i][j]);
     fence();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
+    wait_vmcnt<0>();                             // (and lgkmcnt 0)
     __builtin_amdgcn_s_barrier();
     fence();
 
@@ -1633,7 +1636,8 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     _Float16 *y = (_Float16 *)a.y;
     constexpr int CPR = BN / 8;                  // 8-channel pieces per row
     if constexpr (!POOL) {
-        constexpr int RPT = 256 / CPR, IT = BM / RPT, U = 7;   // rows a pass, passes
+        constexpr int RPT = 256 / CPR, IT = BM / RPT;          // rows a pass, passes
+        constexpr int U = IT % 7 == 0 ? 7 : IT % 4 == 0 ? 4 : IT % 2 == 0 ? 2 : 1;
         static_assert(256 % CPR == 0 && BM % RPT == 0 && IT % U == 0, "copy");
         const int c = tid % CPR, r0 = tid / CPR;
         for (int k = 0; k < IT; k += U) {

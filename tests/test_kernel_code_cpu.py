@@ -1,0 +1,62 @@
+"""The built kernels keep the distances that their inline-asm MFMAs need.
+
+conv_pp issues its matrix instructions as inline assembly, so the compiler
+does not know that a result may only be read (or copied) some wait states
+after its MFMA.  The source keeps every other use of the accumulators behind
+a wait; the compiler may still place register copies, so the instructions of
+the library as built are checked."""
+import os
+import re
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin",
+                       "llvm-objdump")
+AGPR = re.compile(r"\ba(\d+|\[\d+:\d+\])")
+
+
+@pytest.fixture(scope="module")
+def code(tmp_path_factory):
+    """Instructions per conv_pp kernel of libctc.so, in address order."""
+    if not os.path.exists(OBJDUMP):
+        pytest.skip("no llvm-objdump")
+    d = tmp_path_factory.mktemp("code")
+    so = shutil.copy(os.path.join(ROOT, "paper_2609_16742_amd", "libctc.so"), d)
+    subprocess.run([OBJDUMP, "--offloading", so], check=True, cwd=d,
+                   capture_output=True)
+    obj = [f for f in os.listdir(d) if "amdgcn" in f]
+    assert len(obj) == 1, obj
+    out = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn",
+                          os.path.join(d, obj[0])], check=True,
+                         capture_output=True, text=True).stdout
+    fns, cur = {}, None
+    for line in out.splitlines():
+        m = re.match(r"[0-9a-f]+ <(.*)>:$", line)
+        if m:
+            cur = fns.setdefault(m.group(1), []) if "conv_pp" in m.group(1) \
+                else None
+        elif cur is not None and line.startswith("\t"):
+            cur.append(line.split("//")[0].strip())
+    return fns
+
+
+def test_accumulators_of_inline_mfmas_are_touched_only_at_a_distance(code):
+    checked = 0
+    for name, ins in code.items():
+        mfma = [i for i, s in enumerate(ins) if s.startswith("v_mfma")]
+        uses = [i for i, s in enumerate(ins)
+                if AGPR.search(s) and not s.startswith("v_mfma")]
+        waits = [i for i, s in enumerate(ins) if s == "s_nop 11"]
+        if not waits:
+            continue                    # the compiler's own MFMAs
+        checked += 1
+        inside = [ins[i] for i in uses if mfma[0] < i < mfma[-1]]
+        assert not inside, (name, inside[:5])
+        after = [i for i in uses if i > mfma[-1]]
+        assert len(waits) == 1 and mfma[-1] < waits[0] < after[0], name
+        # zeroed accumulators: well ahead of the first MFMA
+        assert mfma[0] - max(i for i in uses if i < mfma[0]) >= 8, name
+    assert checked >= 4, sorted(code)
