@@ -1361,7 +1361,10 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
 __device__ __forceinline__ void mfma16_acc(f32x4 &acc, f16x8 w, f16x8 x) {
     asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
 }
-// (12 wait states cover the 8 passes of a 16x16x32 MFMA)
+__device__ __forceinline__ void mfma16_acc(f32x4 &acc, float w, float x) {
+    asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+a"(acc) : "v"(w), "v"(x));
+}
+// (12 wait states cover the 8 passes of either MFMA)
 __device__ __forceinline__ void mfma_done() {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 11" ::: "memory");
@@ -1369,8 +1372,11 @@ __device__ __forceinline__ void mfma_done() {
 }
 __device__ __forceinline__ void mfma_result(f32x4 &acc) { asm volatile("" : "+a"(acc)); }
 
-template <int BN, int BM, int TW, bool POOL>
-__global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
+template <typename T, int BN, int BM, int TW, bool POOL>
+__device__ __forceinline__ void pp_body(const ConvArgs &a) {
+    constexpr int ES = (int)sizeof(T), KS = 128 / ES;    // k per step
+    typedef typename std::conditional<ES == 2, f16x8, f32x4>::type Frag;
+    static_assert(ES == 2 || !POOL, "pool");
     constexpr int WM = 2, WN = 2;
     constexpr int TM = BM / WM, TN = BN / WN;
     constexpr int IM = TM / 16, IN = TN / 16;
@@ -1378,11 +1384,11 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     // LDS: three stages of pixel rows, two of channel rows
     constexpr int XST = BM * 128, WST = BN * 128, WOFF = 3 * XST;
     constexpr int AR = BM / 32, BR = BN / 32;    // pixel / channel DMAs per wave
-    constexpr int EROW = BN + 8;                 // epilogue row, halves
+    constexpr int EROW = BN + 16 / ES;           // epilogue row, elements
     constexpr int MAIN = WOFF + 2 * WST;
-    constexpr int LDS_BYTES = MAIN > BM * EROW * 2 ? MAIN : BM * EROW * 2;
+    constexpr int LDS_BYTES = MAIN > BM * EROW * ES ? MAIN : BM * EROW * ES;
     static_assert(IN * WN * 16 == BN && IM * WM * 16 == BM, "tile");
-    static_assert(MAIN <= 163840 && BM % 32 == 0 && BN % 32 == 0, "stage");
+    static_assert(LDS_BYTES <= 163840 && BM % 32 == 0 && BN % 32 == 0, "stage");
     static_assert(!POOL || (TW >= 2 && TH % 2 == 0), "pool windows");
     __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
 
@@ -1429,9 +1435,9 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     const int lrow = wave * 8 + (lane >> 3);     // row within a 32-row round
     const int chunk = (lane & 7) ^ (lane >> 3);
     const int Ktot = a.R * a.S * a.Cs;
-    const int nsteps = Ktot / 64;
-    const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * a.Cs * 2);
-    const Rsrc wr = make_rsrc(a.w, (long)a.N * Ktot * 2);
+    const int nsteps = Ktot / KS;
+    const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * a.Cs * ES);
+    const Rsrc wr = make_rsrc(a.w, (long)a.N * Ktot * ES);
 
     // DMA addressing.  Pixel rounds: byte offset of the tap-(0,0) input
     // pixel and (ih0, iw0) packed as two 16-bit fields; rows past the map
@@ -1444,19 +1450,19 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
         const int ih0 = ok ? p * a.stride - a.pad : -16384;
         const int iw0 = q * a.stride - a.pad;
         a_hw[i] = (int)((unsigned)ih0 << 16) | (iw0 & 0xffff);
-        a_pix[i] = ((img * a.H + ih0) * a.W + iw0) * a.Cs * 2 + chunk * 16;
+        a_pix[i] = ((img * a.H + ih0) * a.W + iw0) * a.Cs * ES + chunk * 16;
     }
     // channel rounds (N is a multiple of BN): one lane offset, the round
     // and the step in the scalar offset
-    const int b_base = (n0 + lrow) * Ktot * 2 + chunk * 16;
-    const int b_round = 32 * Ktot * 2;
-    // the tap of the pixel rows issued next (wave-uniform: Cs % 64 == 0)
+    const int b_base = (n0 + lrow) * Ktot * ES + chunk * 16;
+    const int b_round = 32 * Ktot * ES;
+    // the tap of the pixel rows issued next (wave-uniform: Cs % KS == 0)
     int kc = 0, ks = 0, kr = 0;
     auto issue_x = [&](int i, int st) {          // (no short circuits: a branch each)
         const int ih = (a_hw[i] >> 16) + kr, iw = (int)(short)(a_hw[i] & 0xffff) + ks;
         const bool ok = (kr < a.R) & ((unsigned)ih < (unsigned)a.H) &
                         ((unsigned)iw < (unsigned)a.W);
-        const int off = a_pix[i] + ((kr * a.W + ks) * a.Cs + kc) * 2;
+        const int off = a_pix[i] + ((kr * a.W + ks) * a.Cs + kc) * ES;
         dma16(xr, lds + st + (i * 32 + wave * 8) * 128, ok ? off : OOB);
     };
     auto issue_w = [&](int i, int step, int st) {
@@ -1465,7 +1471,7 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
               ok ? i * b_round + step * 128 : 0);
     };
     auto next_tap = [&]() {                      // k = (r, s, c): channels fastest
-        kc += 64;
+        kc += KS;
         const bool tap = kc == a.Cs;
         kc = tap ? 0 : kc;
         ks += tap;
@@ -1490,10 +1496,10 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
         xa[kk] = (wm * TM + fr) * 128 + c;
         wa[kk] = (wn * TN + fr) * 128 + c;
     }
-    f16x8 wf[2][IN], pf[2][IM];
+    Frag wf[2][IN], pf[2][IM];
     auto read = [&](int kk, int i) {             // fragment i of half step kk
-        if (i < IM) pf[kk][i] = *(const f16x8 *)(lds + (xst + xa[kk]) + i * 16 * 128);
-        else wf[kk][i - IM] = *(const f16x8 *)(lds + (wst + wa[kk]) + (i - IM) * 16 * 128);
+        if (i < IM) pf[kk][i] = *(const Frag *)(lds + (xst + xa[kk]) + i * 16 * 128);
+        else wf[kk][i - IM] = *(const Frag *)(lds + (wst + wa[kk]) + (i - IM) * 16 * 128);
     };
     auto fence = [&]() {
         asm volatile("" ::: "memory");
@@ -1519,9 +1525,16 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
 #pragma unroll
             for (int r = i * WPG; kk == 1 && r < (i + 1) * WPG; r++)
                 if (r < BR) issue_w(r, step, to);
+            if constexpr (ES == 2) {
 #pragma unroll
-            for (int j = 0; j < IM; j++)
-                mfma16_acc(acc[i][j], wf[kk][i], pf[kk][j]);
+                for (int j = 0; j < IM; j++) mfma16_acc(acc[i][j], wf[kk][i], pf[kk][j]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < 4; t++)
+#pragma unroll
+                    for (int j = 0; j < IM; j++)
+                        mfma16_acc(acc[i][j], wf[kk][i][t], pf[kk][j][t]);
+            }
             __builtin_amdgcn_sched_barrier(0);
         }
     };
@@ -1591,8 +1604,9 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     // consecutive output pixels) and the copy loop keeps several rows in
     // flight (with a division per row and one row at a time it took about
     // 12 us a tile).
-    _Float16 *ep = (_Float16 *)lds;
-    const _Float16 *res = (const _Float16 *)a.res;
+    T *ep = (T *)lds;
+    const T *res = (const T *)a.res;
+    typedef typename Vec4<T>::t V4;
     // output pixel of tile row r as a row of y (-1: past the map / batch)
     auto out_row = [&](int r) -> int {
         if constexpr (TW > 0) {
@@ -1616,39 +1630,39 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
 #pragma unroll
             for (int j = 0; j < IM; j++) {
                 const int o = out_row(wm * TM + j * 16 + fr);
-                const f16x4 rv = *(const f16x4 *)(res + (size_t)(o < 0 ? 0 : o) * a.N + n0 + nl);
+                const V4 rv = *(const V4 *)(res + (size_t)(o < 0 ? 0 : o) * a.N + n0 + nl);
 #pragma unroll
-                for (int e = 0; e < 4; e++) v[j][e] += (float)rv[e];
+                for (int e = 0; e < 4; e++) v[j][e] += to_f(rv[e]);
             }
         }
 #pragma unroll
         for (int j = 0; j < IM; j++) {
-            f16x4 h;
+            V4 h;
 #pragma unroll
-            for (int e = 0; e < 4; e++) h[e] = (_Float16)(v[j][e] < lim ? 0.f : v[j][e]);
-            *(f16x4 *)(ep + (wm * TM + j * 16 + fr) * EROW + nl) = h;
+            for (int e = 0; e < 4; e++) h[e] = from_f<T>(v[j][e] < lim ? 0.f : v[j][e]);
+            *(V4 *)(ep + (wm * TM + j * 16 + fr) * EROW + nl) = h;
         }
     }
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_waitcnt(0xc07f);
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    _Float16 *y = (_Float16 *)a.y;
-    constexpr int CPR = BN / 8;                  // 8-channel pieces per row
+    T *y = (T *)a.y;
+    constexpr int PV = 16 / ES, CPR = BN / PV;   // 16-byte pieces per row
     if constexpr (!POOL) {
         constexpr int RPT = 256 / CPR, IT = BM / RPT;          // rows a pass, passes
         constexpr int U = IT % 7 == 0 ? 7 : IT % 4 == 0 ? 4 : IT % 2 == 0 ? 2 : 1;
         static_assert(256 % CPR == 0 && BM % RPT == 0 && IT % U == 0, "copy");
         const int c = tid % CPR, r0 = tid / CPR;
         for (int k = 0; k < IT; k += U) {
-            f16x8 v[U];
+            Frag v[U];
 #pragma unroll
             for (int u = 0; u < U; u++)
-                v[u] = *(const f16x8 *)(ep + (r0 + (k + u) * RPT) * EROW + c * 8);
+                v[u] = *(const Frag *)(ep + (r0 + (k + u) * RPT) * EROW + c * PV);
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 const int o = out_row(r0 + (k + u) * RPT);
-                if (o >= 0) *(f16x8 *)(y + (size_t)o * a.N + n0 + c * 8) = v[u];
+                if (o >= 0) *(Frag *)(y + (size_t)o * a.N + n0 + c * PV) = v[u];
             }
         }
     } else {
@@ -1689,12 +1703,65 @@ __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
 }
 
 template <int BN, int BM, int TW, bool POOL>
+__global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
+    pp_body<_Float16, BN, BM, TW, POOL>(a);
+}
+template <int BN, int BM>
+__global__ __launch_bounds__(256, 1) void conv_pp32(ConvArgs a) {
+    pp_body<float, BN, BM, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 128, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 128, 128, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 96, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 128, 96, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 64, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 128, 64, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 32, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 128, 32, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 96, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 64, 96, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 64, 64, 0, false>(a);
+}
+template <>
+__global__ void conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+    pp_body<_Float16, 64, 32, 0, false>(a);
+}
+
+template <int BN, int BM, int TW, bool POOL>
 static hipError_t run_pp(const ConvArgs &a, hipStream_t st) {
     constexpr int TH = TW ? BM / TW : 1;
     long mt = TW ? (long)a.nimg * ((a.P + TH - 1) / TH) * ((a.Q + TW - 1) / TW)
                  : ((long)a.nimg * a.P * a.Q + BM - 1) / BM;
     const long tiles = mt * ((a.N + BN - 1) / BN);
     launch(conv_pp<BN, BM, TW, POOL>, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), st, a);
+    return hipGetLastError();
+}
+
+template <int BN, int BM>
+static hipError_t run_pp32(const ConvArgs &a, hipStream_t st) {
+    const long tiles = ((long)a.nimg * a.P * a.Q + BM - 1) / BM * ((a.N + BN - 1) / BN);
+    launch(conv_pp32<BN, BM>, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), st, a);
+    return hipGetLastError();
+}
+
+// Stride-1 1x1 layers run the same loop as conv_dma's three-stage form.
+template <int BN, int BM>
+static hipError_t run_pp1(const ConvArgs &a, hipStream_t st) {
+    const long tiles = ((long)a.nimg * a.P * a.Q + BM - 1) / BM * ((a.N + BN - 1) / BN);
+    launch(conv_dma<_Float16, BM, BN, 2, 2, 3, true>, dim3((unsigned)((tiles + 7) / 8 * 8)),
+           dim3(256), st, a);
     return hipGetLastError();
 }
 
@@ -2368,7 +2435,7 @@ hipError_t launch_stem_pool(const ConvArgs &a, int PP, int QP, hipStream_t st) {
 enum ConvCfg {
     F32_N16, F32_N32, F32_N64,
     F16V4_N32, F16V4_N64, PW_F16, STEM_F16,
-    PP_256, PP_256_P8, PP_256_P16, PP_128,
+    PP_256, PP_256_P8, PP_256_P16,
     IMG_7, IMG_14,                              // conv_img on 7x7 / 14x14 maps
     IMG_7S2,                                    // conv_img, 14x14 -> 7x7 stride 2
     D_64x32, D_128x64, D_64x64, D_64x128, D_128x128, D_256x256,
@@ -2376,18 +2443,19 @@ enum ConvCfg {
     H_128x64, H_128x64_P16, H_128x128          // conv_dma with the halo A tile
 };
 
-// conv_pp on a layer: fp16 3x3 with whole 64-channel k steps, channel
-// tiles of bn, and enough 224-pixel tiles to fill three quarters of the
-// GPU's CUs, one each.  Measured against conv_dma, which takes the others:
-// bn = 256, 56x56x256 at batch 32 142 -> 115 us; bn = 128 (channel counts
-// that are no multiple of 256), 28x28x128 at batch 64 (224 tiles) 30.4 ->
-// 27.5 us, 56x56 64 -> 128 stride 2 (224) 19.1 -> 16.5, 28x28 192 -> 384 at
-// batch 56 (588) 89.4 -> 85.3; the halo tiles of layers with 64 input
-// channels come first (56x56 64 -> 128 61.7 us against 67.8).
-static bool pp_fits(const ConvArgs &a, int bn) {
+// conv_pp's 256-channel tiles on a layer: fp16 3x3 with whole 64-channel k
+// steps.  One of these tiles per CU and round takes as long as three rounds
+// of 128 x 128 tiles (measured at K = 4608, 28x28x512: 106 us for 224 tiles,
+// 193 for 280; 128 x 128 110, 127, 142 us for 688, 784, 980 tiles) and does
+// 3.5 times their work, so they are taken unless the smaller tiles end in
+// fewer rounds (28x28x512 at batch 40 193 -> 142 us, 56x56x256 at 9 47.5 ->
+// 40.7; not at batch 32: 106 against 127, 116 against 124).  With a fused
+// pool the tiles have to fill three quarters of the CUs.
+static bool pp_fits(const ConvArgs &a) {
     const long M = (long)a.nimg * a.P * a.Q;
-    return a.Cs % 64 == 0 && a.R == 3 && a.S == 3 && a.N % bn == 0 &&
-           (M + 223) / 224 * (a.N / bn) >= 192 &&
+    const long t = (M + 223) / 224 * (a.N / 256), t128 = (M + 127) / 128 * (a.N / 128);
+    return a.Cs % 64 == 0 && a.R == 3 && a.S == 3 && a.N % 256 == 0 &&
+           (a.pool ? t >= 192 : (t128 + 255) / 256 >= 3 * ((t + 255) / 256)) &&
            (long)a.nimg * a.H * a.W * a.Cs * 2 < (1l << 31) &&
            (long)a.N * a.R * a.S * a.Cs * 2 < (1l << 31);
 }
@@ -2459,8 +2527,7 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         if (a.N <= 64) return a.pool ? H_128x64_P16 : H_128x64;
         if (!a.pool) return H_128x128;
     }
-    if (dt == DT_F16 && !a.pool && a.N % 256 && pp_fits(a, 128)) return PP_128;
-    if (dt == DT_F16 && pp_fits(a, 256)) {
+    if (dt == DT_F16 && pp_fits(a)) {
         if (!a.pool) return PP_256;
         // the tile width with fewer tiles (ties: 8)
         const long t8 = pool_tiles(a, 28, 8), t16 = pool_tiles(a, 14, 16);
@@ -2504,28 +2571,104 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
     return pool_cfg(select_conv(dt, b));
 }
 
+// conv_pp's smaller tiles, for the layers of conv_dma that have whole
+// channel tiles and whole 128-byte k steps and are not split over k.  The
+// rows of a table go from the largest tile to the smallest, and a layer takes
+// the first that leaves at least `tiles` of them: 1.5 workgroups per CU keep
+// the matrix cores busy, then smaller tiles spread the pixels over more CUs.
+// conv_dma -> these, measured in graphs, fp16, 3x3: 28x28x128 at batch 8
+// 15.2 -> 9.3 us (32 pixels; 64: 10.6), 16 15.9 -> 11.2 (64), 32 19.2 -> 15.3
+// (64; 96: 16.4), 48 23.8 -> 19.7 (96); 28x28x512 at 16 78 -> 68 (128), 24 118
+// -> 106; 56x56 64 -> 128 stride 2 at 32 12.9 -> 10.5; 28x28 128 -> 256 stride
+// 2, 1x1, at 256 18.9 -> 15.9.  Channel counts that are no multiple of 128:
+// 15x15x64 at batch 50 10.8 -> 6.5, 200 11.5 -> 9.7, 400 16.5 -> 16.2, 30x30
+// 128 -> 64 at 120 36.3 -> 31.7, 19x19 512 -> 64 at 33 47.1 -> 25.1; of these
+// conv_dma stays the faster one with several channel tiles and more than
+// three workgroups per CU (20x20 256 -> 192 at batch 80, 1002 tiles: 42.2 us
+// against 44.0; 501: 28.6 against 25.4).  1x1: 7x7 320 -> 1280 at batch 128
+// 15.5 -> 13.6 us, 2048 -> 512 at 64 23.4 -> 17.6 (64 pixels), 14x14 512 ->
+// 256 at 128 18.0 -> 15.2, 56x56 256 -> 512 at 64 134 -> 121.
+// fp32: 28x28x128 at batch 64 145.9 -> 136.2 us, 14x14x256 163 -> 140 (64 x
+// 64: 150), 14x14 1024 -> 256 1x1 at 16 30.5 -> 24.4; many tiles with a short
+// k pay for the smaller tile's loads: 56x56x64 at 64 140.6 -> 133.4 (64 x 32:
+// 137.1), 56x56 64 -> 256 1x1 133 -> 121 (148).
+struct PpTile {
+    int bn, bm;
+    long tiles;
+    const char *name;
+    hipError_t (*run)(const ConvArgs &, hipStream_t);
+};
+static const PpTile PP_F16[] = {
+    {128, 128, 384, "conv_pp<128, 128, 0, false>", run_pp<128, 128, 0, false>},
+    {128, 96, 384, "conv_pp<128, 96, 0, false>", run_pp<128, 96, 0, false>},
+    {128, 64, 160, "conv_pp<128, 64, 0, false>", run_pp<128, 64, 0, false>},
+    {128, 32, 0, "conv_pp<128, 32, 0, false>", run_pp<128, 32, 0, false>},
+    {64, 96, 384, "conv_pp<64, 96, 0, false>", run_pp<64, 96, 0, false>},
+    {64, 64, 160, "conv_pp<64, 64, 0, false>", run_pp<64, 64, 0, false>},
+    {64, 32, 0, "conv_pp<64, 32, 0, false>", run_pp<64, 32, 0, false>},
+};
+static const PpTile PP_F16_1X1[] = {
+    {128, 128, 384, "conv_dma<_Float16, 128, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 128>},
+    {128, 96, 384, "conv_dma<_Float16, 96, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 96>},
+    {128, 64, 160, "conv_dma<_Float16, 64, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 64>},
+    {128, 32, 0, "conv_dma<_Float16, 32, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 32>},
+    {64, 96, 384, "conv_dma<_Float16, 96, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 96>},
+    {64, 64, 160, "conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 64>},
+    {64, 32, 0, "conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 32>},
+};
+static const PpTile PP_F32[] = {
+    {64, 64, 900, "conv_pp32<64, 64>", run_pp32<64, 64>},
+    {64, 32, 0, "conv_pp32<64, 32>", run_pp32<64, 32>},
+};
+static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
+    const int es = dt == DT_F32 ? 4 : 2;
+    if (a.pool || c < D_64x32 || c > D_256x256 || a.Cs % (128 / es) || a.N % 64 ||
+        (a.part && conv_splitk(dt, a) > 1) ||
+        (long)a.nimg * a.H * a.W * a.Cs * es >= (1l << 31) ||
+        (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
+        return nullptr;
+    const long M = (long)a.nimg * a.P * a.Q;
+    if (dt == DT_F32) {
+        const bool shortk = a.R * a.S * a.Cs <= 640;
+        return &PP_F32[!shortk || (M + 63) / 64 * (a.N / 64) < PP_F32[0].tiles];
+    }
+    const int bn = a.N % 128 ? 64 : 128;
+    if (a.N % 128 > 0 && a.N > 64 && (M + 95) / 96 * (a.N / 64) > 768) return nullptr;
+    const bool pw = a.R == 1 && a.S == 1 && a.stride == 1;
+    for (const PpTile &t : pw ? PP_F16_1X1 : PP_F16)
+        if (t.bn == bn && (M + t.bm - 1) / t.bm * (a.N / bn) >= t.tiles) return &t;
+    return nullptr;
+}
+
 // Whether a layer that select_conv gives to `c` runs on conv_lat at this
 // batch: up to 2048 tiles of 16 pixels x 16 channels, 8 per CU.  Measured
-// there, own kernel -> conv_lat: fp16, one image, 56x56x64 3x3 (784 tiles)
-// 11.3 -> 5.8 us, 28x28x128 (392) 15.5 -> 6.1, 14x14x256 (208) 28.3 -> 5.7,
-// 7x7x512 (128) 15.4 -> 8.3; fp32 28x28x128 32.2 -> 10.5, 14x14x256 59.1 ->
-// 16.3; near the line 56x56x64 11.4 -> 7.1 (two images, 1568 tiles),
-// 14x14x256 28.7 -> 13.4 (eight, 1664), fp32 56x56x64 19.2 -> 10.6.  Above
-// it the tiles that share rows win back what they lose in latency: 56x56x64
-// 11.6 = 11.6 at 3136 tiles, 28x28x72 -> 136 10.8 -> 14.7 at 3528, 14x14 96
-// -> 576 1x1 5.7 -> 9.3 at 3600.  Up to 1024 only: conv_pw's layers, short
-// in k (96 -> 576 5.4 -> 4.6 us at 468 tiles, 5.5 -> 5.6 at 1800), and the
-// 7x7 maps, whose own kernel has small tiles too (512 channels 15.8 -> 12.0
-// us at 800, 16.3 -> 22.4 at 1696).
+// there, other kernel -> conv_lat: fp16, one image, 28x28x128 (392 tiles) 8.6
+// -> 5.9 us, 28x28x512 (1568) 36.1 -> 19.0, 14x14x256 (208) 28.3 -> 5.7,
+// 7x7x512 (128) 15.4 -> 8.3, eight images 14x14x256 (1664) 28.7 -> 13.4; fp32
+// 28x28x128 16.7 -> 10.4, 14x14x256 29.8 -> 16.0, at eight (1568) 31.3 ->
+// 26.1.  Above the line the tiles that share rows win back what they lose in
+// latency: fp32 56x56x64 15.4 -> 18.8 at 3136 tiles, 28x28x72 -> 136 10.8 ->
+// 14.7 at 3528, 14x14 96 -> 576 1x1 5.7 -> 9.3 at 3600.  The line is lower
+// where the other kernel has small tiles itself: 1600 next to conv_pp's in
+// fp16 (28x28x128 8.8 -> 8.4 at 1568, 9.0 -> 11.9 at 2352), or 1024 if k is
+// short too (56x56 64 -> 128 stride 2 6.3 -> 5.7 at 784, 6.4 -> 6.9 at 1568),
+// and 512 next to the 64-channel ones (56x56x64 5.3 -> 5.7 at 784; 28x28 256
+// -> 64, long in k, 10.8 -> 7.0); 1024 next to conv_pw (96 -> 576 5.4 -> 4.6
+// us at 468 tiles, 5.5 -> 5.6 at 1800) and on 7x7 maps (512 channels 15.8 ->
+// 12.0 us at 800, 16.3 -> 22.4 at 1696).
 static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
     const int es = dt == DT_F32 ? 4 : 2;
     if (a.pool || (c < D_64x32 && c != PW_F16 && c != PP_256 && !img_cfg(c))) return false;
     if (a.Cs % (16 / es) || (long)a.nimg * a.H * a.W * a.Cs * es >= (1l << 31) ||
         (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
         return false;
-    const long M = (long)a.nimg * a.P * a.Q;
-    const bool few = c == PW_F16 || c == IMG_7 || c == IMG_7S2;
-    return (M + 15) / 16 * ((a.N + 15) / 16) <= (few ? 1024 : 2048);
+    const long M = (long)a.nimg * a.P * a.Q, tiles = (M + 15) / 16 * ((a.N + 15) / 16);
+    if (c == PW_F16 || c == IMG_7 || c == IMG_7S2) return tiles <= 1024;
+    if (dt == DT_F16 && pp_tile(dt, a, c)) {
+        const bool shortk = a.R * a.S * a.Cs <= 576;
+        return tiles <= (!shortk ? 1600 : a.N % 128 ? 512 : 1024);
+    }
+    return tiles <= 2048;
 }
 
 const char *conv_kernel_name(int dt, const ConvArgs &a) {
@@ -2542,6 +2685,7 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
                  : (uni ? "conv_lat<_Float16, false, true, 1>"
                         : "conv_lat<_Float16, false, false, 1>");
     }
+    if (const PpTile *t = pp_tile(dt, a, cfg)) return t->name;
     switch (cfg) {
     case F32_N16: return "conv_igemm<float, 4, 128, 16, 4, 1>";
     case F32_N32: return "conv_igemm<float, 4, 128, 32, 4, 1>";
@@ -2551,7 +2695,6 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
     case PW_F16: return pw_kernel_name(a);
     case STEM_F16: return stem_kernel_name(a);
     case PP_256: return "conv_pp<256, 224, 0, false>";
-    case PP_128: return "conv_pp<128, 224, 0, false>";
     case PP_256_P8: return "conv_pp<256, 224, 8, true>";
     case PP_256_P16: return "conv_pp<256, 224, 16, true>";
     case IMG_7: return "conv_img<7, false, 1>";
@@ -2650,6 +2793,7 @@ hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
         return hipErrorInvalidValue;
     if (lat_ok(dt, a, c))
         return dt == DT_F32 ? run_lat<float>(a, false, st) : run_lat<_Float16>(a, img_cfg(c), st);
+    if (const PpTile *t = pp_tile(dt, a, c)) return t->run(a, st);
     switch (c) {
     case F32_N16: return run_conv<float, 4, 128, 16, 4, 1>(a, st);
     case F32_N32: return run_conv<float, 4, 128, 32, 4, 1>(a, st);
@@ -2659,7 +2803,6 @@ hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
     case PW_F16: return run_pw(a, st);
     case STEM_F16: return run_stem(a, st);
     case PP_256: return run_pp<256, 224, 0, false>(a, st);
-    case PP_128: return run_pp<128, 224, 0, false>(a, st);
     case PP_256_P8: return run_pp<256, 224, 8, true>(a, st);
     case PP_256_P16: return run_pp<256, 224, 16, true>(a, st);
     case IMG_7: return run_img<7, false>(a, st);

@@ -9,7 +9,7 @@ pytestmark = pytest.mark.gpu
 # dtype, C, H, W, K, k, stride, residual, images small / large, conv_lat form
 CASES = [
     # whole 64-channel steps: one tap per step, several steps per tap
-    ("f16", 64, 56, 56, 64, 3, 1, True, 2, 8, "<_Float16, false, true, 1>"),
+    ("f16", 64, 24, 24, 64, 3, 1, True, 2, 40, "<_Float16, false, true, 1>"),
     ("f16", 128, 29, 27, 72, 3, 2, False, 1, 33, "<_Float16, false, true, 1>"),
     # chunks of one step in different taps (72 and 8 channels), k tails,
     # 4 of 16 channels in the last tile, pixel tails
@@ -87,50 +87,77 @@ def test_small_batches_give_the_bits_of_large_ones(case):
     assert err <= (2.0 ** -11 if dtype == "f16" else 1e-5) * ref.norm()
 
 
-# C, H, W, K, stride, residual, images large (conv_pp) / small (conv_dma)
-WIDE = [
-    # one 128-channel tile, ragged last pixel tile; two tiles; 9, 18, 27 steps
-    (64, 41, 35, 128, 2, True, 120, 90),
-    (128, 27, 29, 128, 1, True, 55, 12),
-    (192, 27, 29, 384, 1, False, 20, 8),
-    (256, 29, 27, 256, 1, True, 56, 10),
+# dtype, C, H, W, K, kernel, stride, residual, images, tile; ragged last pixel
+# tiles, one or several channel tiles, 1 (fewer than the stages) to 36 steps
+D3 = "conv_dma<_Float16, %d, %d, 2, 2, 3, true, 0, false, 0>"
+TILES = [
+    ("f16", 64, 25, 27, 128, 3, 1, True, 6, "conv_pp<128, 32, 0, false>"),
+    ("f16", 64, 27, 25, 128, 1, 2, False, 40, "conv_pp<128, 32, 0, false>"),
+    ("f16", 128, 27, 25, 256, 3, 2, True, 40, "conv_pp<128, 64, 0, false>"),
+    ("f16", 256, 15, 17, 384, 1, 2, True, 90, "conv_pp<128, 64, 0, false>"),
+    ("f16", 128, 29, 31, 128, 3, 1, True, 45, "conv_pp<128, 96, 0, false>"),
+    ("f16", 192, 19, 21, 512, 3, 1, False, 33, "conv_pp<128, 128, 0, false>"),
+    ("f16", 64, 39, 41, 128, 1, 2, True, 140, "conv_pp<128, 128, 0, false>"),
+    ("f16", 64, 25, 27, 64, 3, 1, False, 13, "conv_pp<64, 32, 0, false>"),
+    ("f16", 128, 25, 27, 192, 3, 1, True, 7, "conv_pp<64, 64, 0, false>"),
+    ("f16", 64, 27, 25, 64, 5, 2, True, 250, "conv_pp<64, 96, 0, false>"),
+    ("f16", 128, 41, 35, 256, 3, 2, True, 120, "conv_pp<256, 224, 0, false>"),
+    ("f16", 256, 29, 27, 256, 3, 1, True, 57, "conv_pp<256, 224, 0, false>"),
+    ("f16", 192, 13, 13, 384, 1, 1, True, 110, D3 % (128, 128)),
+    ("f16", 320, 13, 13, 384, 1, 1, False, 80, D3 % (96, 128)),
+    ("f16", 576, 13, 13, 128, 1, 1, True, 70, D3 % (64, 128)),
+    ("f16", 192, 13, 13, 256, 1, 1, False, 13, D3 % (32, 128)),
+    ("f16", 320, 13, 13, 192, 1, 1, True, 80, D3 % (96, 64)),
+    ("f16", 384, 13, 13, 64, 1, 1, False, 70, D3 % (64, 64)),
+    ("f16", 192, 13, 13, 64, 1, 1, True, 40, D3 % (32, 64)),
+    ("f32", 96, 27, 25, 64, 3, 1, True, 13, "conv_pp32<64, 32>"),
+    ("f32", 96, 27, 25, 128, 1, 2, False, 90, "conv_pp32<64, 32>"),
+    ("f32", 128, 13, 15, 192, 3, 1, False, 20, "conv_pp32<64, 32>"),
+    ("f32", 64, 49, 51, 64, 3, 1, True, 53, "conv_pp32<64, 64>"),
+    ("f32", 32, 49, 51, 64, 1, 1, False, 54, "conv_pp32<64, 64>"),
 ]
 
 
-@pytest.mark.parametrize("case", WIDE)
-def test_wide_tiles_give_the_bits_of_small_ones(case):
+@pytest.mark.parametrize("case", TILES)
+def test_tiles_of_every_size_give_the_bits_of_one_image(case):
     import paper_2609_16742_amd as P
     ctc = P.ctc
-    C, H, W, K, st, res, large, small = case
-    print("wide tiles", case, flush=True)
+    dtype, C, H, W, K, k, st, res, n, name = case
+    print("tiles", case, flush=True)
+    tdt = torch.float16 if dtype == "f16" else torch.float32
     g = torch.Generator(device="cuda")
-    g.manual_seed(C + K)
-    p, q = ((d - 1) // st + 1 for d in (H, W))
-    d = ctc.layer_desc(C, K, 3, 3, st, 1, 1, 1, ctc.CTC_ROLE_SUM)
+    g.manual_seed(TILES.index(case))
+    pad = k // 2
+    p, q = ((d + 2 * pad - k) // st + 1 for d in (H, W))
+    d = ctc.layer_desc(C, K, k, k, st, pad, 1, 1, ctc.CTC_ROLE_SUM)
+    dt = ctc.DTYPES[dtype]
 
     def rnd(*shape):
         return torch.randn(shape, device="cuda", generator=g)
 
-    x, w = rnd(large, H, W, C).half(), (rnd(K, 3, 3, C) * 0.05).half()
+    x = rnd(n, H, W, C).to(tdt)
+    w = (rnd(K, k, k, C) / (k * k * C) ** 0.5).to(tdt)
     scale, shift = rnd(K), rnd(K)
-    r = rnd(large, p, q, K).half() if res else None
-    x[1, H // 2, W // 2, 5] = float("inf")       # stays in its 3x3 windows
-
-    def run(n):
-        y = torch.full((n, p, q, K), float("nan"), device="cuda").half()
-        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x[:n], w, scale, shift,
-                               None if r is None else r[:n], 1, y)
-        return y
-
-    bn = 256 if K % 256 == 0 else 128
-    names = [ctc.ctc_conv2d_kernel_name(d, ctc.CTC_F16, n, H, W)
-             for n in (large, small)]
-    assert names[0] == "conv_pp<%d, 224, 0, false>" % bn
-    assert names[1].startswith("conv_dma<")
-    yl, ys = run(large), run(small)
-    torch.cuda.synchronize()
-    a, b = (t.cpu().numpy().view(np.uint16) for t in (yl[:small], ys))
-    nan = np.isnan(a.view(np.float16)) & np.isnan(b.view(np.float16))
-    assert np.array_equal(a[~nan], b[~nan]) and nan.sum() < 9 * K + 1
-    # every row past the small batch is written, and the inf stayed put
-    assert bool(torch.isfinite(yl[small:]).all())
+    r = rnd(n, p, q, K).to(tdt) if res else None
+    y = torch.full((n, p, q, K), float("nan"), device="cuda").to(tdt)
+    assert ctc.ctc_conv2d_kernel_name(d, dt, n, H, W) == name
+    ctc.ctc_conv2d_forward(d, dt, n, H, W, x, w, scale, shift, r, 1, y)
+    # the first, the last and a middle image alone
+    for i in (0, n // 2, n - 1):
+        one = torch.full((1, p, q, K), float("nan"), device="cuda").to(tdt)
+        ctc.ctc_conv2d_forward(d, dt, 1, H, W, x[i:i + 1], w, scale, shift,
+                               None if r is None else r[i:i + 1], 1, one)
+        bits = torch.int16 if dtype == "f16" else torch.int32
+        assert torch.equal(y[i:i + 1].view(bits), one.view(bits)), i
+    ref = torch.nn.functional.conv2d(
+        x.cpu().double().permute(0, 3, 1, 2), w.cpu().double().permute(0, 3, 1, 2),
+        stride=st, padding=pad)
+    ref = (ref * scale.cpu().double()[:, None, None]
+           + shift.cpu().double()[:, None, None])
+    if res:
+        ref += r.cpu().double().permute(0, 3, 1, 2)
+    ref = ref.relu()
+    err = (y.cpu().double().permute(0, 3, 1, 2) - ref).flatten(1).norm(dim=1)
+    # every image: one rounding to 11 bits, or sums of K <= 2304 in fp32
+    assert bool((err <= (2.0 ** -11 if dtype == "f16" else 1e-5)
+                 * ref.flatten(1).norm(dim=1)).all())
