@@ -2443,6 +2443,14 @@ enum ConvCfg {
     H_128x64, H_128x64_P16, H_128x128          // conv_dma with the halo A tile
 };
 
+// conv_pp's addressing: whole 128-byte k steps, 31-bit byte offsets, and input
+// coordinates (past the pads too) in 16 bits
+static bool pp_addr_ok(const ConvArgs &a, int es) {
+    return a.Cs % (128 / es) == 0 && a.H < 16384 && a.W < 16384 && a.R < 8192 && a.S < 8192 &&
+           a.pad < 8192 && (long)a.nimg * a.H * a.W * a.Cs * es < (1l << 31) &&
+           (long)a.N * a.R * a.S * a.Cs * es < (1l << 31);
+}
+
 // conv_pp's 256-channel tiles on a layer: fp16 3x3 with whole 64-channel k
 // steps.  One of these tiles per CU and round takes as long as three rounds
 // of 128 x 128 tiles (measured at K = 4608, 28x28x512: 106 us for 224 tiles,
@@ -2454,10 +2462,8 @@ enum ConvCfg {
 static bool pp_fits(const ConvArgs &a) {
     const long M = (long)a.nimg * a.P * a.Q;
     const long t = (M + 223) / 224 * (a.N / 256), t128 = (M + 127) / 128 * (a.N / 128);
-    return a.Cs % 64 == 0 && a.R == 3 && a.S == 3 && a.N % 256 == 0 &&
-           (a.pool ? t >= 192 : (t128 + 255) / 256 >= 3 * ((t + 255) / 256)) &&
-           (long)a.nimg * a.H * a.W * a.Cs * 2 < (1l << 31) &&
-           (long)a.N * a.R * a.S * a.Cs * 2 < (1l << 31);
+    return a.R == 3 && a.S == 3 && a.N % 256 == 0 && pp_addr_ok(a, 2) &&
+           (a.pool ? t >= 192 : (t128 + 255) / 256 >= 3 * ((t + 255) / 256));
 }
 
 // Spatial tiles of th x tw output pixels for a conv with the 2x2 / 2 max
@@ -2621,11 +2627,8 @@ static const PpTile PP_F32[] = {
     {64, 32, 0, "conv_pp32<64, 32>", run_pp32<64, 32>},
 };
 static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
-    const int es = dt == DT_F32 ? 4 : 2;
-    if (a.pool || c < D_64x32 || c > D_256x256 || a.Cs % (128 / es) || a.N % 64 ||
-        (a.part && conv_splitk(dt, a) > 1) ||
-        (long)a.nimg * a.H * a.W * a.Cs * es >= (1l << 31) ||
-        (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
+    if (a.pool || c < D_64x32 || c > D_256x256 || a.N % 64 ||
+        !pp_addr_ok(a, dt == DT_F32 ? 4 : 2) || (a.part && conv_splitk(dt, a) > 1))
         return nullptr;
     const long M = (long)a.nimg * a.P * a.Q;
     if (dt == DT_F32) {

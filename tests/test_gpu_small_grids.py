@@ -161,3 +161,31 @@ def test_tiles_of_every_size_give_the_bits_of_one_image(case):
     # every image: one rounding to 11 bits, or sums of K <= 2304 in fp32
     assert bool((err <= (2.0 ** -11 if dtype == "f16" else 1e-5)
                  * ref.flatten(1).norm(dim=1)).all())
+
+
+# maps taller or wider than the 16-bit coordinates of conv_pp's tiles
+@pytest.mark.parametrize("dtype,H,W,K", [("f16", 33001, 2, 64), ("f16", 2, 33001, 256),
+                                         ("f32", 2, 16500, 64), ("f32", 33001, 2, 64)])
+def test_long_maps_keep_their_kernel(dtype, H, W, K):
+    import paper_2609_16742_amd as P
+    ctc = P.ctc
+    print("long map", dtype, H, W, K, flush=True)
+    d = ctc.layer_desc(64, K, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
+    dt = ctc.DTYPES[dtype]
+    assert "conv_pp" not in ctc.ctc_conv2d_kernel_name(d, dt, 1, H, W)
+    tdt = torch.float16 if dtype == "f16" else torch.float32
+    g = torch.Generator(device="cuda")
+    g.manual_seed(K)
+    x = torch.randn((1, H, W, 64), device="cuda", generator=g).to(tdt)
+    w = (torch.randn((K, 3, 3, 64), device="cuda", generator=g) / 24).to(tdt)
+    one, zero = torch.ones(K, device="cuda"), torch.zeros(K, device="cuda")
+    y = torch.full((1, H, W, K), float("nan"), device="cuda").to(tdt)
+    ctc.ctc_conv2d_forward(d, dt, 1, H, W, x, w, one, zero, None, 0, y)
+    # the far end of the map
+    hs, ws = slice(-20 if H > 20 else 0, None), slice(-20 if W > 20 else 0, None)
+    ref = torch.nn.functional.conv2d(
+        x[:, hs, ws].cpu().double().permute(0, 3, 1, 2),
+        w.cpu().double().permute(0, 3, 1, 2), padding=1).permute(0, 2, 3, 1)
+    ref, got = (ref[:, 1:], y[:, -19:]) if H > 20 else (ref[:, :, 1:], y[:, :, -19:])
+    err = (got.cpu().double() - ref).norm()
+    assert err <= (2.0 ** -11 if dtype == "f16" else 1e-5) * ref.norm()
