@@ -37,7 +37,8 @@ def code(tmp_path_factory):
         m = re.match(r"[0-9a-f]+ <(.*)>:$", line)
         if m:
             cur = fns.setdefault(m.group(1), []) \
-                if re.search("conv_pp|conv_dma.*Li2ELi2ELi3E", m.group(1)) else None
+                if re.search("conv_pp|conv_dma.*Li2ELi2E(Li3E|Li2ELb1ELi16ELb1ELi0E)",
+                             m.group(1)) else None
         elif cur is not None and line.startswith("\t"):
             cur.append(line.split("//")[0].strip())
     return fns
@@ -46,17 +47,18 @@ def code(tmp_path_factory):
 def test_accumulators_of_inline_mfmas_are_touched_only_at_a_distance(code):
     checked = 0
     for name, ins in code.items():
-        mfma = [i for i, s in enumerate(ins) if s.startswith("v_mfma")]
-        uses = [i for i, s in enumerate(ins)
-                if AGPR.search(s) and not s.startswith("v_mfma")]
         waits = [i for i, s in enumerate(ins) if s == "s_nop 11"]
         if not waits:
             continue                    # the compiler's own MFMAs
         checked += 1
-        inside = [ins[i] for i in uses if mfma[0] < i < mfma[-1]]
-        assert not inside, (name, inside[:5])
-        after = [i for i in uses if i > mfma[-1]]
-        assert len(waits) == 1 and mfma[-1] < waits[0] < after[0], name
-        # zeroed accumulators: well ahead of the first MFMA
-        assert mfma[0] - max(i for i in uses if i < mfma[0]) >= 8, name
-    assert checked >= 19, sorted(code)
+        assert len(waits) == 1, name
+        # the loop up to the wait is one basic block
+        top = max(i for i in range(waits[0]) if re.match("s_c?branch", ins[i]))
+        mfma = [i for i in range(top, waits[0]) if ins[i].startswith("v_mfma")]
+        uses = [i for i, s in enumerate(ins[:waits[0]])
+                if AGPR.search(s) and not s.startswith("v_mfma")]
+        assert len(mfma) >= 4 and "a[" in ins[mfma[0]], name
+        near = [ins[i] for i in uses if i > mfma[0] - 8]
+        # (zeroed accumulators: well ahead of the first MFMA)
+        assert not near, (name, near[:5])
+    assert checked >= 20, sorted(code)
