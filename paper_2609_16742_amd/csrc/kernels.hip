@@ -358,6 +358,22 @@ __device__ __forceinline__ void dma16(Rsrc r, void *lds, int voff, int soff = 0)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (LdsPtr)lds, 16, voff, soff, 0, 0);
 }
 
+// 16 bytes per lane at buffer offset `voff` + `soff` (as above); past the end
+// loads return zero and stores write nothing
+__device__ __forceinline__ f16x8 buf_load16(Rsrc r, int voff, int soff) {
+    return __builtin_bit_cast(f16x8, __builtin_amdgcn_raw_buffer_load_b128(r, voff, soff, 0));
+}
+__device__ __forceinline__ void buf_store16(Rsrc r, f16x8 v, int voff, int soff) {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), r, voff, soff, 0);
+}
+typedef __attribute__((ext_vector_type(2))) unsigned u32x2;
+__device__ __forceinline__ u32x2 buf_load8(Rsrc r, int voff, int soff) {
+    return __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
+}
+__device__ __forceinline__ void buf_store8(Rsrc r, u32x2 v, int voff, int soff) {
+    __builtin_amdgcn_raw_buffer_store_b64(v, r, voff, soff, 0);
+}
+
 // The epilogue of the LDS-staged implicit-GEMM convolution (conv_dma), run
 // by all NW = WM * WN waves once the K loop is done and the LDS is free.  Every lane holds the MFMA accumulators acc[i][j] of its
 // wave's TN x TM sub-tile (channel tile i, pixel tile j); pixel(r, img, p, q)
@@ -1080,6 +1096,324 @@ static hipError_t run_img(const ConvArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// fp16 3x3 stride-1 convolution of 64 input channels, for maps large enough
+// to give every wave a few rows: filters in registers, pixels streamed.
+// What bounds a tile kernel here is its short k (9 steps): each tile pays
+// for its input's and first filters' latency and for its epilogue, and reads
+// 6 fragments per 8 MFMAs from the LDS.  Here a wave keeps the 36 fragments
+// of 32 channels' filters for its whole life (eight waves a CU) and walks
+// down a strip of 16 output pixels: an input row of 18 pixels comes by DMA
+// into the wave's own ring of six rows (no barriers), gives 6 fragments
+// (3 column shifts x 2 channel halves) and feeds 36 MFMAs, those of the
+// three output rows that it touches; the row that it completes leaves from
+// the registers.  Per output the taps come in order (r, s, c), as in every
+// other kernel of these layers, so the bits are theirs.
+// The channel of MFMA row m of half i is 8 (m / 4) + 4 i + m % 4, so that a
+// lane ends up with 8 consecutive channels, one 16-byte store.
+// The output rows (pairs of rows with the pool) of all strips are split
+// evenly over the waves; a wave crosses into the next strip where its part
+// does, and the ring runs on across that.
+// Measured (batch 32, conv_dma's halo tiles -> this): 224x224x64 with the pool
+// 176 -> 109 us, 112x112 64 -> 128 101 -> 59 us (1.0 PFLOP/s); 56x56x64 at 64
+// with a residual 31.4 -> 24.6.  What is left over is the matrix core at the
+// clock that its power allows and, on small maps, the filters' way into the
+// registers, about 3 us.
+// ---------------------------------------------------------------------------
+constexpr int ROWS_RING = 6, ROWS_SLOT = 3072;   // rows in flight; 24 pixels
+constexpr int ROWS_LDS = 4 * ROWS_RING * ROWS_SLOT + 512;
+
+template <bool POOL, bool WIDE>
+__device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
+    constexpr int RING = ROWS_RING * ROWS_SLOT, SC = 4 * RING;
+    static_assert(RING == 16 * 9 * 128, "16 channels' filters fill a ring");
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int fr = lane & 15, fg = lane >> 4;
+    // 64 channels a workgroup; the channel blocks of the same pixels are
+    // neighbours on one XCD
+    const int nb = (a.N + 63) / 64, per = (int)gridDim.x >> 3;
+    const int lb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
+    const int cb = lb % nb * 64, g = wave & 1;
+    const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * 128);
+    const Rsrc wr = make_rsrc(a.w, (long)a.N * 1152);
+
+    // the filters of MFMA rows m of (channel half g, i) through ring 2 g + i
+#pragma unroll
+    for (int d = 0; d < 18; d++) {
+        const int row = d * 8 + (lane >> 3), m = row / 9, rs = row - m * 9;
+        const int ch = cb + (wave >> 1) * 32 + 8 * (m >> 2) + 4 * (wave & 1) + (m & 3);
+        dma16(wr, lds + wave * RING + d * 1024,
+              ch * 1152 + rs * 128 + (((lane & 7) ^ (m & 7)) << 4));
+    }
+    if (tid < 64) {
+        const bool ok = cb + tid < a.N;          // (filters past N read zeros)
+        *(float *)(lds + SC + tid * 4) = ok ? a.scale[cb + tid] : 0.f;
+        *(float *)(lds + SC + 256 + tid * 4) = ok ? a.shift[cb + tid] : 0.f;
+    }
+    wait_vmcnt<0>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    f16x8 wf[9][2][2];                           // [tap][channel half of 32][i]
+#pragma unroll
+    for (int i = 0; i < 2; i++)
+#pragma unroll
+        for (int t = 0; t < 9; t++)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+                wf[t][c][i] = *(const f16x8 *)(lds + (2 * g + i) * RING + (fr * 9 + t) * 128 +
+                                               (((c * 4 + fg) ^ (fr & 7)) << 4));
+    asm volatile("" ::: "memory");
+    wait_vmcnt<0>();                             // (lgkmcnt 0)
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+
+    // this wave's units [pos, end): output rows, or pairs of them
+    constexpr int UR = POOL ? 2 : 1;
+    const int sx = (a.Q + 15) >> 4, U = a.P / UR;
+    const int nr = (int)gridDim.x / nb * 2, ri = lb / nb * 2 + (wave >> 1);
+    const long T = (long)a.nimg * sx * U;
+    const int pos = (int)(T * ri / nr), todo = (int)(T * (ri + 1) / nr) - pos;
+    if (todo == 0) return;
+    // a place in the stream: strip (image, first column) and output rows y0 ..
+    // y0 + rows of the current segment, its input row k of rows + 2, units
+    // left after it, byte offsets of input row y0 - 1 + k and of the output
+    // row (a pair's pooled one) that row k completes
+    const int xrow = a.W * 128, QO = a.Q / UR, yrow = QO * a.N * 2;
+    const int nl = cb + g * 32 + fg * 8;         // this lane's channels
+    struct Place { int img, x0, y0, rows, k, left, xoff, yoff; };
+    auto start = [&](Place &p, int y0, int units) {
+        p.y0 = y0;
+        p.k = 0;
+        p.rows = (p.left < units ? p.left : units) * UR;
+        p.left -= p.rows / UR;
+        p.xoff = (p.img * a.H + y0 - 1) * xrow;
+        p.yoff = (p.img * U + y0 / UR) * yrow;
+    };
+    // this lane's output offset in a row, 8 channels of one pixel (of even
+    // ones with the pool)
+    auto out_lane = [&](const Place &p) {
+        const int x = p.x0 + fr;
+        const bool ok = x / UR < QO && (!POOL || !(fr & 1)) && nl < a.N;
+        return ok ? (x / UR * a.N + nl) * 2 : OOB;
+    };
+    // WIDE (N % 8 == 0): 8 channels at once, else 4 and 4
+    auto put = [&](Rsrc r, f16x8 v, int voff, int soff) {
+        if constexpr (WIDE) {
+            buf_store16(r, v, voff, soff);
+        } else {
+            const u32x4 t = __builtin_bit_cast(u32x4, v);
+            buf_store8(r, (u32x2){t[0], t[1]}, voff, soff);
+            buf_store8(r, (u32x2){t[2], t[3]}, nl + 8 <= a.N ? voff + 8 : OOB, soff);
+        }
+    };
+    auto get = [&](Rsrc r, int voff, int soff) -> f16x8 {
+        if constexpr (WIDE) return buf_load16(r, voff, soff);
+        const u32x2 l = buf_load8(r, voff, soff);
+        const u32x2 h = buf_load8(r, nl + 8 <= a.N ? voff + 8 : OOB, soff);
+        return __builtin_bit_cast(f16x8, (u32x4){l[0], l[1], h[0], h[1]});
+    };
+    const int px = lane >> 3;
+    int xlane[3];                                // this lane's part of an input row
+    auto in_lane = [&](const Place &p) {
+#pragma unroll
+        for (int d = 0; d < 3; d++) {
+            const int x = p.x0 - 1 + px + d * 8;
+            const bool ok = (unsigned)x < (unsigned)a.W && (d < 2 || px < 2);
+            xlane[d] = ok ? x * 128 + (((lane & 7) ^ px) << 4) : OOB;
+        }
+    };
+    auto next_segment = [&](Place &p) {
+        p.x0 += 16;
+        if (p.x0 >= a.Q) { p.x0 = 0; p.img++; }
+        start(p, 0, U);
+    };
+    Place rd, in;                                // consumed / sent next
+    rd.left = todo;
+    {
+        const int strip = pos / U, y = pos - strip * U;
+        rd.img = strip / sx;
+        rd.x0 = (strip - rd.img * sx) * 16;
+        start(rd, y * UR, U - y);
+        in = rd;
+    }
+    in_lane(in);
+    int ylane = out_lane(rd), rlane = ylane;
+    char *ring = lds + wave * RING;
+    const int xsize = a.nimg * a.H * xrow, ysize = a.nimg * U * yrow;
+    f16x8 rv[ROWS_RING];                         // residual rows of the slots
+    // row in.k of the stream into a slot (past the map or the end: zeros, by
+    // an empty buffer); pixel px of the slot holds column x0 - 1 + px, its
+    // 16-byte chunks swizzled
+    auto issue = [&](auto sc) {
+        constexpr int slot = decltype(sc)::value;
+        const bool ok = (in.rows > 0) & ((unsigned)(in.y0 - 1 + in.k) < (unsigned)a.H);
+        const Rsrc r = make_rsrc(a.x, ok ? xsize : 0);
+        const int soff = ok ? in.xoff : 0;
+#pragma unroll
+        for (int d = 0; d < 3; d++) dma16(r, ring + slot * ROWS_SLOT + d * 1024, xlane[d], soff);
+        if (!POOL && a.res) {
+            const bool rok = (in.rows > 0) & (in.k >= 2);
+            rv[slot] = get(make_rsrc(a.res, rok ? ysize : 0), rlane,
+                           rok ? in.yoff + (in.k - 2) * yrow : 0);
+        }
+        in.xoff += xrow;
+        if (++in.k == in.rows + 2) {
+            next_segment(in);
+            in_lane(in);
+            rlane = out_lane(in);
+        }
+    };
+    int fo[3][2];                                // fragment offsets in a slot
+#pragma unroll
+    for (int s = 0; s < 3; s++)
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+            fo[s][c] = (fr + s) * 128 + (((c * 4 + fg) ^ ((fr + s) & 7)) << 4);
+
+    const float lim = a.relu ? 0.f : -__builtin_inff();
+    const char *scp = lds + SC + (g * 32 + fg * 8) * 4;
+    f32x4 acc[3][2];
+#pragma unroll
+    for (int r = 0; r < 3; r++) acc[r][0] = acc[r][1] = (f32x4)(0.f);
+    f16x8 hold = {};
+    // Ring slot u = input row k of the segment; acc[u % 3] starts output row
+    // k with tap row 0, acc[(u + 2) % 3] is row k - 1, acc[(u + 1) % 3] is
+    // row k - 2, which this row completes.  (With the pool every segment has
+    // an even number of input rows: u and k have the same parity.)  The
+    // store of a row that a segment does not have goes to an empty buffer.
+    // Returns whether the stream is done.
+    auto step = [&](auto uc) -> bool {
+        constexpr int u = decltype(uc)::value;
+        asm volatile("" ::: "memory");
+        wait_vmcnt<3 * (ROWS_RING - 2)>();
+        asm volatile("" ::: "memory");
+        f16x8 pf[3][2];
+#pragma unroll
+        for (int s = 0; s < 3; s++)
+#pragma unroll
+            for (int c = 0; c < 2; c++)
+                pf[s][c] = *(const f16x8 *)(ring + u * ROWS_SLOT + fo[s][c]);
+        issue(std::integral_constant<int, (u + ROWS_RING - 1) % ROWS_RING>());
+        auto taps = [&](auto rc, f32x4 (&o)[2]) {
+            constexpr int r = decltype(rc)::value;
+#pragma unroll
+            for (int s = 0; s < 3; s++)
+#pragma unroll
+                for (int c = 0; c < 2; c++)
+#pragma unroll
+                    for (int i = 0; i < 2; i++)
+                        o[i] = __builtin_amdgcn_mfma_f32_16x16x32_f16(
+                            wf[r * 3 + s][c][i], pf[s][c],
+                            r + s + c == 0 ? (f32x4)(0.f) : o[i], 0, 0, 0);
+        };
+        if (rd.k >= 2) taps(std::integral_constant<int, 2>(), acc[(u + 1) % 3]);
+        if ((unsigned)(rd.k - 1) < (unsigned)rd.rows)
+            taps(std::integral_constant<int, 1>(), acc[(u + 2) % 3]);
+        if (rd.k < rd.rows) taps(std::integral_constant<int, 0>(), acc[u % 3]);
+        float v[8];
+#pragma unroll
+        for (int i = 0; i < 2; i++) {
+            const f32x4 t = acc[(u + 1) % 3][i] * *(const f32x4 *)(scp + i * 16) +
+                            *(const f32x4 *)(scp + 256 + i * 16);
+#pragma unroll
+            for (int e = 0; e < 4; e++) v[i * 4 + e] = t[e];
+        }
+        if (!POOL && a.res) {
+#pragma unroll
+            for (int e = 0; e < 8; e++) v[e] += (float)rv[u][e];
+        }
+        f16x8 h;
+#pragma unroll
+        for (int e = 0; e < 8; e++) {
+            // rounded to fp32 first, as everywhere else (v_fma_mixlo_f16
+            // would round once)
+            asm("" : "+v"(v[e]));
+            h[e] = (_Float16)(v[e] < lim ? 0.f : v[e]);
+        }
+        const Rsrc yr = make_rsrc(a.y, rd.k >= 2 ? ysize : 0);
+        if constexpr (!POOL) {
+            put(yr, h, ylane, rd.k >= 2 ? rd.yoff + (rd.k - 2) * yrow : 0);
+        } else if constexpr (u % 2 == 0) {
+            hold = h;
+        } else {
+            // 2x2 stride-2 max pool of the stored (fp16) values, window
+            // order and NaN rule of maxpool_fixed; the window's right
+            // column is in the next lane
+            auto right = [](f16x8 q) {
+                u32x4 t = __builtin_bit_cast(u32x4, q);
+#pragma unroll
+                for (int e = 0; e < 4; e++)
+                    t[e] = (unsigned)__builtin_amdgcn_mov_dpp((int)t[e], 0xb1, 0xf, 0xf, true);
+                return __builtin_bit_cast(f16x8, t);
+            };
+            const f16x8 w4[4] = {hold, right(hold), h, right(h)};
+            f16x8 ov;
+#pragma unroll
+            for (int e = 0; e < 8; e++) {
+                _Float16 best = w4[0][e];
+                const bool nan = __builtin_isunordered(w4[0][e], w4[1][e]) |
+                                 __builtin_isunordered(w4[2][e], w4[3][e]);
+#pragma unroll
+                for (int k = 1; k < 4; k++) best = w4[k][e] > best ? w4[k][e] : best;
+                ov[e] = nan ? (_Float16)__builtin_nanf("") : best;
+            }
+            put(yr, ov, ylane, rd.k >= 2 ? rd.yoff + (rd.k - 2) / 2 * yrow : 0);
+        }
+        if (++rd.k == rd.rows + 2) {
+            if (rd.left == 0) return true;
+            next_segment(rd);
+            ylane = out_lane(rd);
+        }
+        return false;
+    };
+    issue(std::integral_constant<int, 0>());
+    issue(std::integral_constant<int, 1>());
+    issue(std::integral_constant<int, 2>());
+    issue(std::integral_constant<int, 3>());
+    issue(std::integral_constant<int, 4>());
+    static_assert(ROWS_RING == 6, "the slots above and below");
+    for (;;) {
+        if (step(std::integral_constant<int, 0>())) break;
+        if (step(std::integral_constant<int, 1>())) break;
+        if (step(std::integral_constant<int, 2>())) break;
+        if (step(std::integral_constant<int, 3>())) break;
+        if (step(std::integral_constant<int, 4>())) break;
+        if (step(std::integral_constant<int, 5>())) break;
+    }
+    wait_vmcnt<0>();                             // no DMA outlives the workgroup's LDS
+}
+
+// Under the names of conv_dma's halo form.
+template <>
+__global__ __launch_bounds__(256, 2) void conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>(
+    ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
+    rows_body<false, true>(a, lds);
+}
+template <>
+__global__ __launch_bounds__(256, 2) void conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>(
+    ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
+    rows_body<true, true>(a, lds);
+}
+template <bool POOL>
+__global__ __launch_bounds__(256, 2) void conv_rows4(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
+    rows_body<POOL, false>(a, lds);
+}
+template <bool POOL>
+static hipError_t run_rows(const ConvArgs &a, hipStream_t st) {
+    const int nb = (a.N + 63) / 64;
+    const dim3 grid((unsigned)(8 * (64 / nb * nb)));
+    if (a.N % 8)
+        launch(conv_rows4<POOL>, grid, dim3(256), st, a);
+    else
+        launch(conv_dma<_Float16, 128, POOL ? 64 : 128, 2, 2, 2, true, 16, POOL, 1>, grid,
+               dim3(256), st, a);
+    return hipGetLastError();
+}
+
 template <typename T, int BM, int BN, int WM, int WN, int NS, bool XCD = true,
           int TW = 0, bool POOL = false, int HALO = 0>
 static hipError_t run_dma(const ConvArgs &a, hipStream_t st) {
@@ -1702,24 +2036,19 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
             if (n >= a.N || pp >= PP || pq >= QP) continue;
             const int r00 = (pr / PW) * 2 * TW + (pr % PW) * 2;
             const int rr[4] = {r00, r00 + 1, r00 + TW, r00 + TW + 1};
-            float best[8];
-            bool nan[8];
+            f16x8 v[4];
 #pragma unroll
-            for (int e = 0; e < 8; e++) { best[e] = -__builtin_inff(); nan[e] = false; }
-#pragma unroll
-            for (int k = 0; k < 4; k++) {
-                const f16x8 v = *(const f16x8 *)(ep + rr[k] * EROW + c * 8);
-#pragma unroll
-                for (int e = 0; e < 8; e++) {
-                    const float f = (float)v[e];
-                    if (f != f) nan[e] = true;
-                    else if (f > best[e]) best[e] = f;
-                }
-            }
+            for (int k = 0; k < 4; k++) v[k] = *(const f16x8 *)(ep + rr[k] * EROW + c * 8);
             f16x8 ov;
 #pragma unroll
-            for (int e = 0; e < 8; e++)
-                ov[e] = (_Float16)(nan[e] ? __builtin_nanf("") : best[e]);
+            for (int e = 0; e < 8; e++) {
+                _Float16 best = v[0][e];
+                bool nan = __builtin_isunordered(v[0][e], v[1][e]) |
+                           __builtin_isunordered(v[2][e], v[3][e]);
+#pragma unroll
+                for (int k = 1; k < 4; k++) best = v[k][e] > best ? v[k][e] : best;
+                ov[e] = nan ? (_Float16)__builtin_nanf("") : best;
+            }
             _Float16 *o = y + ((size_t)(img0 * PP + pp) * QP + pq) * a.N + n;
             if (n + 8 <= a.N) *(f16x8 *)o = ov;
             else *(f16x4 *)o = (f16x4){ov[0], ov[1], ov[2], ov[3]};
@@ -1738,37 +2067,37 @@ __global__ __launch_bounds__(256, 1) void conv_pp32(ConvArgs a) {
     pp_body<float, BN, BM, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 128, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 128, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 128>()];
     pp_body<_Float16, 128, 128, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 96, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 96, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 96>()];
     pp_body<_Float16, 128, 96, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 64, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 64>()];
     pp_body<_Float16, 128, 64, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 32, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 32>()];
     pp_body<_Float16, 128, 32, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 96, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 96, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 96>()];
     pp_body<_Float16, 64, 96, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 64>()];
     pp_body<_Float16, 64, 64, 0, false>(a, lds);
 }
 template <>
-__global__ void conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 32>()];
     pp_body<_Float16, 64, 32, 0, false>(a, lds);
 }
@@ -2474,7 +2803,8 @@ enum ConvCfg {
     IMG_7S2,                                    // conv_img, 14x14 -> 7x7 stride 2
     D_64x32, D_128x64, D_64x64, D_64x128, D_128x128, D_256x256,
     D_128x64_P16, D_128x128_P16,
-    H_128x64, H_128x64_P16, H_128x128          // conv_dma with the halo A tile
+    H_128x64,                                  // conv_dma with the halo A tile
+    ROWS, ROWS_P                               // rows_body
 };
 
 // conv_pp's 256-channel tiles on a layer: fp16 3x3 with whole 64-channel k
@@ -2505,15 +2835,32 @@ static bool pool_waste_ok(const ConvArgs &a, int th, int tw) {
 }
 
 // conv_dma's halo mode (8 x 16 pixel tiles, one 64-channel plane): fp16
-// 3x3 stride 1 pad 1 on 64 stored input channels, at most 128 output
+// 3x3 stride 1 pad 1 on 64 stored input channels, at most 64 output
 // channels, tiles that fill the GPU with at most 1/6 of their pixels past
 // the map
 static bool halo_ok(const ConvArgs &a) {
     return a.Cs == 64 && a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 &&
-           a.N <= 128 && a.P == a.H && a.Q == a.W && pool_tiles(a, 8, 16) >= 256 &&
+           a.N <= 64 && a.P == a.H && a.Q == a.W && pool_tiles(a, 8, 16) >= 256 &&
            pool_waste_ok(a, 8, 16) &&
            (long)a.nimg * a.H * a.W * a.Cs * 2 < (1l << 31) &&
            (long)a.N * 9 * a.Cs * 2 < (1l << 31);
+}
+
+// rows_body on a layer: whole strips of 16 columns but for a sixth of the
+// work, and at least 3072 strip rows of 64 output channels (3 per wave: its
+// filters take as long as about two).  conv_pp's small tiles -> this there:
+// 56x56x64 at batch 8 7.9 -> 8.4 us, 12 9.4 -> 9.5 (2688 rows), 16 11.1 -> 10.3
+// (3584), 64 32.5 -> 25.3; 28x28x64 at 32 7.8 -> 8.3 (1792), 64 11.1 -> 10.4;
+// 112x112 64 -> 192 at 2 16.5 -> 12.3, 64 -> 256 at 32 154 -> 105; 40x40x64 (a
+// sixth past the map) at 32 11.6 -> 11.2, 20x20 64 -> 128 (3/8) at 400 39.2 ->
+// 40.3.  Channel counts that fill a part of 64, conv_dma -> this: 60x60 64 ->
+// 40 at 64 30.0 -> 21.0 us, 64 -> 96 54.7 -> 37.0, 64 -> 100 67 -> 46.
+static bool rows_ok(const ConvArgs &a) {
+    const long strips = (a.Q + 15) / 16, px = (long)a.nimg * a.H * a.W;
+    return !a.pool && a.Cs == 64 && a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 &&
+           a.N % 4 == 0 && a.N <= 256 && strips * 16 * 5 <= a.Q * 6l &&
+           a.nimg * strips * a.P * ((a.N + 63) / 64) >= 3072 && px * 128 < (1l << 31) &&
+           px * a.N * 2 < (1l << 31);
 }
 
 static ConvCfg select_conv(int dt, const ConvArgs &a) {
@@ -2534,11 +2881,6 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         }
         return a.N <= 32 ? F16V4_N32 : F16V4_N64;
     }
-    // 3x3 stride-1 layers on 64 input channels: the halo tile (each input
-    // pixel moves to LDS once instead of once per tap; measured with the
-    // same bits: VGG-16 conv1_2 (+ pool) 200 -> 190 us, conv2_1 105 -> 95 us,
-    // ResNet-18's 56x56x64 convs 35.7 -> 27.2 us; with 128 input channels
-    // and with a pool on 128 output channels no faster, so not used there)
     // 7x7 and 14x14 maps take the whole-image kernel, from the layer's shape
     // alone (measured in the networks: ResNet-18's 7x7 stage, 512 channels
     // at batch 64, 40-50 us per conv as a split implicit GEMM plus its
@@ -2555,9 +2897,15 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         a.W == 14 && a.P == 7 && a.Q == 7 && a.Cs % 64 == 0 && a.N % 64 == 0 && !a.pool &&
         (long)a.nimg * a.H * a.W * a.Cs * 2 < (1l << 31) && (long)a.N * 9 * a.Cs * 2 < (1l << 31))
         return IMG_7S2;
+    // 3x3 stride-1 layers on 64 input channels: the filters in registers
+    // (rows_body), or, for channel counts that neither it nor conv_pp's
+    // tiles take, the halo tile (each input pixel moves to LDS once instead
+    // of once per tap; with 128 input channels and with a pool on 128 output
+    // channels no faster)
+    if (dt == DT_F16 && rows_ok(a)) return ROWS;
     if (dt == DT_F16 && halo_ok(a)) {
-        if (a.N <= 64) return a.pool ? H_128x64_P16 : H_128x64;
-        if (!a.pool) return H_128x128;
+        if (a.pool) return ROWS_P;
+        if (a.N < 64) return H_128x64;
     }
     if (dt == DT_F16 && pp_fits(a)) {
         if (!a.pool) return PP_256;
@@ -2594,7 +2942,7 @@ static bool img_cfg(ConvCfg c) { return c == IMG_7 || c == IMG_14 || c == IMG_7S
 
 static bool pool_cfg(ConvCfg c) {
     return c == PP_256_P8 || c == PP_256_P16 || c == D_128x64_P16 || c == D_128x128_P16 ||
-           c == H_128x64_P16;
+           c == ROWS_P;
 }
 
 bool conv_pool_ok(int dt, const ConvArgs &a) {
@@ -2744,8 +3092,10 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
     case D_128x128_P16: return f ? "conv_dma<float, 128, 128, 2, 2, 2, true, 16, true, 0>"
                                  : "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, true, 0>";
     case H_128x64: return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, false, 1>";
-    case H_128x64_P16: return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>";
-    case H_128x128: return "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>";
+    case ROWS: if (a.N % 8) return "conv_rows4<false>";
+               return "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>";
+    case ROWS_P: if (a.N % 8) return "conv_rows4<true>";
+                 return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>";
     default: return f ? "conv_dma<float, 128, 128, 2, 2, 2, true, 0, false, 0>"
                       : "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 0, false, 0>";
     }
@@ -2762,13 +3112,8 @@ static hipError_t launch_dma(ConvCfg c, const ConvArgs &a, hipStream_t st) {
     case D_128x64_P16: return run_dma<T, 128, 64, 2, 2, 2, true, 16, true>(a, st);
     case D_128x128_P16: return run_dma<T, 128, 128, 2, 2, 2, true, 16, true>(a, st);
     case H_128x64:
-    case H_128x64_P16:
-    case H_128x128:
-        if constexpr (sizeof(T) == 2) {
-            if (c == H_128x64) return run_dma<T, 128, 64, 2, 2, 2, true, 16, false, 1>(a, st);
-            if (c == H_128x64_P16) return run_dma<T, 128, 64, 2, 2, 2, true, 16, true, 1>(a, st);
-            return run_dma<T, 128, 128, 2, 2, 2, true, 16, false, 1>(a, st);
-        }
+        if constexpr (sizeof(T) == 2)
+            return run_dma<T, 128, 64, 2, 2, 2, true, 16, false, 1>(a, st);
         return hipErrorInvalidValue;
     default: return run_dma<T, 128, 128, 2, 2, 2>(a, st);
     }
@@ -2834,6 +3179,8 @@ hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
     case PP_256: return run_pp<256, 224, 0, false>(a, st);
     case PP_256_P8: return run_pp<256, 224, 8, true>(a, st);
     case PP_256_P16: return run_pp<256, 224, 16, true>(a, st);
+    case ROWS: return run_rows<false>(a, st);
+    case ROWS_P: return run_rows<true>(a, st);
     case IMG_7: return run_img<7, false>(a, st);
     case IMG_14: return run_img<14, false>(a, st);
     case IMG_7S2: return run_img<7, false, 2>(a, st);

@@ -189,3 +189,87 @@ def test_long_maps_keep_their_kernel(dtype, H, W, K):
     ref, got = (ref[:, 1:], y[:, -19:]) if H > 20 else (ref[:, :, 1:], y[:, :, -19:])
     err = (got.cpu().double() - ref).norm()
     assert err <= (2.0 ** -11 if dtype == "f16" else 1e-5) * ref.norm()
+
+
+# n, H, W, C, K: conv and 2x2 pool in one kernel; odd maps, strips of 16
+# pixels that end in the map's middle, parts of strips per wave, even rows
+# only, one and several 64-channel blocks
+POOLED = [
+    (9, 60, 60, 64, 64), (28, 47, 47, 64, 64), (5, 131, 45, 64, 64), (1, 182, 257, 64, 64),
+    (9, 60, 60, 64, 40), (9, 60, 60, 64, 36), (9, 60, 60, 64, 24), (8, 64, 96, 128, 128), (30, 38, 47, 192, 128),
+    (15, 39, 93, 96, 128), (30, 28, 56, 128, 256), (40, 42, 30, 128, 256),
+]
+
+
+@pytest.mark.parametrize("case", POOLED)
+def test_fused_pool_gives_the_bits_of_the_pooled_convolution(case):
+    import paper_2609_16742_amd as P
+    ctc = P.ctc
+    n, H, W, C, K = case
+    print("pooled", case, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(POOLED.index(case))
+    d = ctc.layer_desc(C, K, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
+    x = torch.randn((n, H, W, C), device="cuda", generator=g).half()
+    w = (torch.randn((K, 3, 3, C), device="cuda", generator=g) / (9 * C) ** 0.5).half()
+    scale = torch.rand(K, device="cuda", generator=g) + 0.5
+    shift = torch.randn(K, device="cuda", generator=g)
+    x[0, H // 2, W // 2, 3] = float("inf")
+    for relu in (0, 1):
+        y = torch.full((n, H, W, K), float("nan"), device="cuda").half()
+        yp = torch.full((n, H // 2, W // 2, K), 7.0, device="cuda").half()
+        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, None, relu, y)
+        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, None, relu, yp,
+                               pool=2)
+        win = y[:, :H // 2 * 2, :W // 2 * 2].unflatten(1, (-1, 2)).unflatten(3, (-1, 2))
+        ref = win.float().amax(dim=(2, 4)).half()      # amax keeps a NaN
+        assert torch.equal(torch.isnan(ref), torch.isnan(yp))
+        ok = ~torch.isnan(ref)
+        assert torch.equal(ref[ok], yp[ok])
+
+
+# n, H, W, K, residual: layers of 64 input channels with filters in registers
+ROWS = [
+    (16, 60, 60, 64, True), (9, 60, 60, 128, False), (34, 33, 61, 64, False),
+    (5, 150, 97, 64, True), (1, 181, 257, 128, True), (200, 18, 16, 64, True),
+    (10, 57, 94, 192, False), (5, 57, 45, 256, True), (19, 57, 45, 40, True),
+    (19, 57, 45, 12, True), (19, 45, 77, 32, False),
+    (20, 60, 44, 96, False), (8, 60, 60, 100, True), (30, 33, 61, 68, True),
+]
+
+
+@pytest.mark.parametrize("case", ROWS)
+def test_filters_in_registers_give_the_bits_of_one_image(case):
+    import paper_2609_16742_amd as P
+    ctc = P.ctc
+    n, H, W, K, res = case
+    print("rows", case, flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(H)
+    d = ctc.layer_desc(64, K, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
+    assert ctc.ctc_conv2d_kernel_name(d, ctc.CTC_F16, n, H, W) == (
+        "conv_rows4<false>" if K % 8 else
+        "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>")
+    x = torch.randn((n, H, W, 64), device="cuda", generator=g).half()
+    w = (torch.randn((K, 3, 3, 64), device="cuda", generator=g) / 24).half()
+    scale = torch.rand(K, device="cuda", generator=g) + 0.5
+    shift = torch.randn(K, device="cuda", generator=g)
+    r = torch.randn((n, H, W, K), device="cuda", generator=g).half() if res else None
+    y = torch.full((n, H, W, K), float("nan"), device="cuda").half()
+    ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, r, 1, y)
+    if n > 1:
+        # single images and bands of rows run on kernels with smaller tiles
+        for i in (0, n // 2, n - 1):
+            one = torch.full((1, H, W, K), float("nan"), device="cuda").half()
+            ctc.ctc_conv2d_forward(d, ctc.CTC_F16, 1, H, W, x[i:i + 1], w, scale, shift,
+                                   None if r is None else r[i:i + 1], 1, one)
+            assert torch.equal(y[i:i + 1].view(torch.int16), one.view(torch.int16)), i
+    ref = torch.nn.functional.conv2d(x.cpu().float().permute(0, 3, 1, 2),
+                                     w.cpu().float().permute(0, 3, 1, 2), padding=1)
+    ref = (ref * scale.cpu()[:, None, None] + shift.cpu()[:, None, None]).permute(0, 2, 3, 1)
+    if res:
+        ref = ref + r.cpu().float()
+    ref = ref.relu()
+    err = (y.cpu().float() - ref).flatten(2).norm(dim=2)
+    # every row of every image: one rounding to 11 bits
+    assert bool((err <= 2.0 ** -11 * ref.flatten(2).norm(dim=2)).all())
