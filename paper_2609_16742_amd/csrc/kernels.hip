@@ -552,10 +552,10 @@ __device__ __forceinline__ void dma_epilogue(const ConvArgs &a,
         }
     }
 }
-// conv_pp's addressing: whole 128-byte k steps, 31-bit byte offsets, and input
-// coordinates (past the pads too) in 16 bits
+// conv_pp's addressing: 31-bit byte offsets and input coordinates (past the
+// pads too) in 16 bits
 __host__ __device__ static inline bool pp_addr_ok(const ConvArgs &a, int es) {
-    return a.Cs % (128 / es) == 0 && a.H < 16384 && a.W < 16384 && a.R < 8192 && a.S < 8192 &&
+    return a.H < 16384 && a.W < 16384 && a.R < 8192 && a.S < 8192 &&
            a.pad < 8192 && (long)a.nimg * a.H * a.W * a.Cs * es < (1l << 31) &&
            (long)a.N * a.R * a.S * a.Cs * es < (1l << 31);
 }
@@ -566,7 +566,7 @@ constexpr int pp_lds() {
     constexpr int MAIN = (3 * BM + 2 * BN) * 128, EPI = BM * (BN * (int)sizeof(T) + 16);
     return MAIN > EPI ? MAIN : EPI;
 }
-template <typename T, int BN, int BM, int TW, bool POOL>
+template <typename T, int BN, int BM, int TW, bool POOL, bool RAG = false>
 __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds);
 
 template <typename T, int BM, int BN, int WM, int WN, int NS, bool XCD,
@@ -612,7 +612,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_dma(ConvArgs a) {
     constexpr int LDS_PP = PP ? pp_lds<T, BN, BM>() : 0;
     __shared__ __attribute__((aligned(16))) char lds[LDS_DMA > LDS_PP ? LDS_DMA : LDS_PP];
     if constexpr (PP) {
-        if (pp_addr_ok(a, ES) && a.N % BN == 0) {
+        if (pp_addr_ok(a, ES) && a.Cs % KS == 0 && a.N % BN == 0) {
             pp_body<T, BN, BM, TW, POOL>(a, lds);
             return;
         }
@@ -1734,7 +1734,7 @@ __device__ __forceinline__ void mfma_done() {
 }
 __device__ __forceinline__ void mfma_result(f32x4 &acc) { asm volatile("" : "+a"(acc)); }
 
-template <typename T, int BN, int BM, int TW, bool POOL>
+template <typename T, int BN, int BM, int TW, bool POOL, bool RAG>
 __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
     constexpr int ES = (int)sizeof(T), KS = 128 / ES;    // k per step
     typedef typename std::conditional<ES == 2, f16x8, f32x4>::type Frag;
@@ -1794,7 +1794,7 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
     const int lrow = wave * 8 + (lane >> 3);     // row within a 32-row round
     const int chunk = (lane & 7) ^ (lane >> 3);
     const int Ktot = a.R * a.S * a.Cs;
-    const int nsteps = Ktot / KS;
+    const int nsteps = RAG ? (Ktot + KS - 1) / KS : Ktot / KS;
     const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * a.Cs * ES);
     const Rsrc wr = make_rsrc(a.w, (long)a.N * Ktot * ES);
 
@@ -1809,14 +1809,22 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
         const int ih0 = ok ? p * a.stride - a.pad : -16384;
         const int iw0 = q * a.stride - a.pad;
         a_hw[i] = (int)((unsigned)ih0 << 16) | (iw0 & 0xffff);
-        a_pix[i] = ((img * a.H + ih0) * a.W + iw0) * a.Cs * ES + chunk * 16;
+        a_pix[i] = ((img * a.H + ih0) * a.W + iw0) * a.Cs * ES + (RAG ? 0 : chunk * 16);
     }
-    // channel rounds (N is a multiple of BN): one lane offset, the round
-    // and the step in the scalar offset
+    // channel rounds (N is a multiple of BN, or RAG): one lane offset, the
+    // round and the step in the scalar offset, which stays inside the array
     const int b_base = (n0 + lrow) * Ktot * ES + chunk * 16;
     const int b_round = 32 * Ktot * ES;
-    // the tap of the pixel rows issued next (wave-uniform: Cs % KS == 0)
+    // the tap of the pixel rows issued next: wave-uniform (Cs % KS == 0), or,
+    // RAG, that of this lane's chunk (Cs >= KS: a step crosses one tap at most)
     int kc = 0, ks = 0, kr = 0;
+    if constexpr (RAG) {
+        kc = chunk * (16 / ES);
+        ks = kc / a.Cs;
+        kc -= ks * a.Cs;
+        kr = ks / a.S;
+        ks -= kr * a.S;
+    }
     auto issue_x = [&](int i, int st) {          // (no short circuits: a branch each)
         const int ih = (a_hw[i] >> 16) + kr, iw = (int)(short)(a_hw[i] & 0xffff) + ks;
         const bool ok = (kr < a.R) & ((unsigned)ih < (unsigned)a.H) &
@@ -1825,14 +1833,20 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
         dma16(xr, lds + st + (i * 32 + wave * 8) * 128, ok ? off : OOB);
     };
     auto issue_w = [&](int i, int step, int st) {
-        const bool ok = step < nsteps;           // past the layer: zeros
-        dma16(wr, lds + st + (i * 32 + wave * 8) * 128, ok ? b_base : OOB,
-              ok ? i * b_round + step * 128 : 0);
+        char *to = lds + st + (i * 32 + wave * 8) * 128;
+        if constexpr (RAG) {                     // past k or N: zeros, lane by lane
+            const bool ok = (step * KS + chunk * (16 / ES) < Ktot) &
+                            (n0 + i * 32 + lrow < a.N);
+            dma16(wr, to, ok ? b_base + i * b_round + step * 128 : OOB);
+        } else {
+            const bool ok = step < nsteps;       // past the layer: zeros
+            dma16(wr, to, ok ? b_base : OOB, ok ? i * b_round + step * 128 : 0);
+        }
     };
     auto next_tap = [&]() {                      // k = (r, s, c): channels fastest
         kc += KS;
-        const bool tap = kc == a.Cs;
-        kc = tap ? 0 : kc;
+        const bool tap = RAG ? kc >= a.Cs : kc == a.Cs;
+        kc = RAG ? kc - (tap ? a.Cs : 0) : tap ? 0 : kc;
         ks += tap;
         const bool row = ks == a.S;
         ks = row ? 0 : ks;
@@ -1980,8 +1994,10 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
 #pragma unroll
     for (int i = 0; i < IN; i++) {
         const int nl = wn * TN + i * 16 + fg * 4;
-        const f32x4 sc = *(const f32x4 *)(a.scale + n0 + nl);
-        const f32x4 sh = *(const f32x4 *)(a.shift + n0 + nl);
+        // (RAG: the channels past N are not stored)
+        const int nc = RAG ? min(n0 + nl, a.N - 4) : n0 + nl;
+        const f32x4 sc = *(const f32x4 *)(a.scale + nc);
+        const f32x4 sh = *(const f32x4 *)(a.shift + nc);
         f32x4 v[IM];
 #pragma unroll
         for (int j = 0; j < IM; j++) v[j] = acc[i][j] * sc + sh;
@@ -1989,7 +2005,7 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
 #pragma unroll
             for (int j = 0; j < IM; j++) {
                 const int o = out_row(wm * TM + j * 16 + fr);
-                const V4 rv = *(const V4 *)(res + (size_t)(o < 0 ? 0 : o) * a.N + n0 + nl);
+                const V4 rv = *(const V4 *)(res + (size_t)(o < 0 ? 0 : o) * a.N + nc);
 #pragma unroll
                 for (int e = 0; e < 4; e++) v[j][e] += to_f(rv[e]);
             }
@@ -2021,7 +2037,8 @@ __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
 #pragma unroll
             for (int u = 0; u < U; u++) {
                 const int o = out_row(r0 + (k + u) * RPT);
-                if (o >= 0) *(Frag *)(y + (size_t)o * a.N + n0 + c * PV) = v[u];
+                if (o >= 0 && (!RAG || n0 + c * PV < a.N))
+                    *(Frag *)(y + (size_t)o * a.N + n0 + c * PV) = v[u];
             }
         }
     } else {
@@ -2060,6 +2077,12 @@ template <int BN, int BM, int TW, bool POOL>
 __global__ __launch_bounds__(256, 1) void conv_pp(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, BN, BM>()];
     pp_body<_Float16, BN, BM, TW, POOL>(a, lds);
+}
+// (RAG: channel counts that are no multiples of the step or of the tile)
+template <typename T, int BN, int BM>
+__global__ __launch_bounds__(256, 1) void conv_ppr(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<T, BN, BM>()];
+    pp_body<T, BN, BM, 0, false, true>(a, lds);
 }
 template <int BN, int BM>
 __global__ __launch_bounds__(256, 1) void conv_pp32(ConvArgs a) {
@@ -2102,6 +2125,37 @@ __global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 64, 2, 2, 3, tr
     pp_body<_Float16, 64, 32, 0, false>(a, lds);
 }
 
+template <>
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 128, 128, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 128>()];
+    pp_body<_Float16, 128, 128, 0, false, true>(a, lds);
+}
+template <>
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 128, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 64>()];
+    pp_body<_Float16, 128, 64, 0, false, true>(a, lds);
+}
+template <>
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 128, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 32>()];
+    pp_body<_Float16, 128, 32, 0, false, true>(a, lds);
+}
+template <>
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 96, 64, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 96>()];
+    pp_body<_Float16, 64, 96, 0, false, true>(a, lds);
+}
+template <>
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 64, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 64>()];
+    pp_body<_Float16, 64, 64, 0, false, true>(a, lds);
+}
+template <>
+__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 64, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 32>()];
+    pp_body<_Float16, 64, 32, 0, false, true>(a, lds);
+}
+
 template <int BN, int BM, int TW, bool POOL>
 static hipError_t run_pp(const ConvArgs &a, hipStream_t st) {
     constexpr int TH = TW ? BM / TW : 1;
@@ -2119,11 +2173,19 @@ static hipError_t run_pp32(const ConvArgs &a, hipStream_t st) {
     return hipGetLastError();
 }
 
-// Stride-1 1x1 layers run the same loop as conv_dma's three-stage form.
-template <int BN, int BM>
+template <typename T, int BN, int BM>
+static hipError_t run_ppr(const ConvArgs &a, hipStream_t st) {
+    const long tiles = ((long)a.nimg * a.P * a.Q + BM - 1) / BM * ((a.N + BN - 1) / BN);
+    launch(conv_ppr<T, BN, BM>, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), st, a);
+    return hipGetLastError();
+}
+
+// Stride-1 1x1 layers run the same loop as conv_dma's three-stage form (NS =
+// 4: RAG).
+template <int BN, int BM, int NS = 3>
 static hipError_t run_pp1(const ConvArgs &a, hipStream_t st) {
     const long tiles = ((long)a.nimg * a.P * a.Q + BM - 1) / BM * ((a.N + BN - 1) / BN);
-    launch(conv_dma<_Float16, BM, BN, 2, 2, 3, true>, dim3((unsigned)((tiles + 7) / 8 * 8)),
+    launch(conv_dma<_Float16, BM, BN, 2, 2, NS, true>, dim3((unsigned)((tiles + 7) / 8 * 8)),
            dim3(256), st, a);
     return hipGetLastError();
 }
@@ -2818,7 +2880,7 @@ enum ConvCfg {
 static bool pp_fits(const ConvArgs &a) {
     const long M = (long)a.nimg * a.P * a.Q;
     const long t = (M + 223) / 224 * (a.N / 256), t128 = (M + 127) / 128 * (a.N / 128);
-    return a.R == 3 && a.S == 3 && a.N % 256 == 0 && pp_addr_ok(a, 2) &&
+    return a.R == 3 && a.S == 3 && a.Cs % 64 == 0 && a.N % 256 == 0 && pp_addr_ok(a, 2) &&
            (a.pool ? t >= 192 : (t128 + 255) / 256 >= 3 * ((t + 255) / 256));
 }
 
@@ -2951,9 +3013,9 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
     return pool_cfg(select_conv(dt, b));
 }
 
-// conv_pp's smaller tiles, for the layers of conv_dma that have whole
-// channel tiles and whole 128-byte k steps and are not split over k.  The
-// rows of a table go from the largest tile to the smallest, and a layer takes
+// conv_pp's smaller tiles, for the layers of conv_dma that have at least one
+// 128-byte k step of input channels and whole 16-byte pieces of output
+// channels and are not split over k.  The rows of a table go from the largest tile to the smallest, and a layer takes
 // the first that leaves at least `tiles` of them: 1.5 workgroups per CU keep
 // the matrix cores busy, then smaller tiles spread the pixels over more CUs.
 // conv_dma -> these, measured in graphs, fp16, 3x3: 28x28x128 at batch 8
@@ -2962,11 +3024,17 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
 // -> 106; 56x56 64 -> 128 stride 2 at 32 12.9 -> 10.5; 28x28 128 -> 256 stride
 // 2, 1x1, at 256 18.9 -> 15.9.  Channel counts that are no multiple of 128:
 // 15x15x64 at batch 50 10.8 -> 6.5, 200 11.5 -> 9.7, 400 16.5 -> 16.2, 30x30
-// 128 -> 64 at 120 36.3 -> 31.7, 19x19 512 -> 64 at 33 47.1 -> 25.1; of these
-// conv_dma stays the faster one with several channel tiles and more than
-// three workgroups per CU (20x20 256 -> 192 at batch 80, 1002 tiles: 42.2 us
-// against 44.0; 501: 28.6 against 25.4).  1x1: 7x7 320 -> 1280 at batch 128
-// 15.5 -> 13.6 us, 2048 -> 512 at 64 23.4 -> 17.6 (64 pixels), 14x14 512 ->
+// 128 -> 64 at 120 36.3 -> 31.7, 19x19 512 -> 64 at 33 47.1 -> 25.1.  Channel
+// counts that fill neither tile (64 channels past a multiple of 128, or parts
+// of 64) take padded 128-channel tiles where 384 of them are left and the
+// padding is below 30%, and channels that end within a step (RAG) cost a few
+// address instructions: 20x20 256 -> 192 at 160 79.7 -> 74.6, 28x28 256 -> 320
+// at 64 103 -> 90, 96 -> 320 54.7 -> 47.1, 96 -> 96 23.0 -> 19.0, 57x53 72 -> 136
+// at 24 39.9 -> 37.9 (28x28 at 64 with a residual 30.7 -> 31.7), 7x7 960 -> 160
+// 1x1 at 128 11.7 -> 9.8.  conv_dma stays for stride-1 1x1 layers that write
+// more than they compute: with a residual 14x14 96 -> 576 at 256 39.5 us
+// against 43.3, 17x17 192 -> 320 at 64 12.0 against 13.2.
+// 1x1: 7x7 320 -> 1280 at batch 128 15.5 -> 13.6 us, 2048 -> 512 at 64 23.4 -> 17.6 (64 pixels), 14x14 512 ->
 // 256 at 128 18.0 -> 15.2, 56x56 256 -> 512 at 64 134 -> 121.
 // fp32: 28x28x128 at batch 64 145.9 -> 136.2 us, 14x14x256 163 -> 140 (64 x
 // 64: 150), 14x14 1024 -> 256 1x1 at 16 30.5 -> 24.4; many tiles with a short
@@ -2996,25 +3064,57 @@ static const PpTile PP_F16_1X1[] = {
     {64, 64, 160, "conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 64>},
     {64, 32, 0, "conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 32>},
 };
+static const PpTile PPR_F16[] = {
+    {128, 128, 384, "conv_ppr<_Float16, 128, 128>", run_ppr<_Float16, 128, 128>},
+    {128, 64, 160, "conv_ppr<_Float16, 128, 64>", run_ppr<_Float16, 128, 64>},
+    {128, 32, 0, "conv_ppr<_Float16, 128, 32>", run_ppr<_Float16, 128, 32>},
+    {64, 96, 384, "conv_ppr<_Float16, 64, 96>", run_ppr<_Float16, 64, 96>},
+    {64, 64, 160, "conv_ppr<_Float16, 64, 64>", run_ppr<_Float16, 64, 64>},
+    {64, 32, 0, "conv_ppr<_Float16, 64, 32>", run_ppr<_Float16, 64, 32>},
+};
+static const PpTile PPR_F16_1X1[] = {
+    {128, 128, 384, "conv_dma<_Float16, 128, 128, 2, 2, 4, true, 0, false, 0>", run_pp1<128, 128, 4>},
+    {128, 64, 160, "conv_dma<_Float16, 64, 128, 2, 2, 4, true, 0, false, 0>", run_pp1<128, 64, 4>},
+    {128, 32, 0, "conv_dma<_Float16, 32, 128, 2, 2, 4, true, 0, false, 0>", run_pp1<128, 32, 4>},
+    {64, 96, 384, "conv_dma<_Float16, 96, 64, 2, 2, 4, true, 0, false, 0>", run_pp1<64, 96, 4>},
+    {64, 64, 160, "conv_dma<_Float16, 64, 64, 2, 2, 4, true, 0, false, 0>", run_pp1<64, 64, 4>},
+    {64, 32, 0, "conv_dma<_Float16, 32, 64, 2, 2, 4, true, 0, false, 0>", run_pp1<64, 32, 4>},
+};
+static const PpTile PPR_F32[] = {
+    {64, 64, 900, "conv_ppr<float, 64, 64>", run_ppr<float, 64, 64>},
+    {64, 32, 0, "conv_ppr<float, 64, 32>", run_ppr<float, 64, 32>},
+};
 static const PpTile PP_F32[] = {
     {64, 64, 900, "conv_pp32<64, 64>", run_pp32<64, 64>},
     {64, 32, 0, "conv_pp32<64, 32>", run_pp32<64, 32>},
 };
 static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
-    if (a.pool || c < D_64x32 || c > D_256x256 || a.N % 64 ||
-        !pp_addr_ok(a, dt == DT_F32 ? 4 : 2) || (a.part && conv_splitk(dt, a) > 1))
+    const int ks = dt == DT_F32 ? 32 : 64;
+    if (a.pool || c < D_64x32 || c > D_256x256 || !pp_addr_ok(a, dt == DT_F32 ? 4 : 2) ||
+        (a.part && conv_splitk(dt, a) > 1))
         return nullptr;
-    const long M = (long)a.nimg * a.P * a.Q;
-    if (dt == DT_F32) {
-        const bool shortk = a.R * a.S * a.Cs <= 640;
-        return &PP_F32[!shortk || (M + 63) / 64 * (a.N / 64) < PP_F32[0].tiles];
-    }
-    const int bn = a.N % 128 ? 64 : 128;
-    if (a.N % 128 > 0 && a.N > 64 && (M + 95) / 96 * (a.N / 64) > 768) return nullptr;
     const bool pw = a.R == 1 && a.S == 1 && a.stride == 1;
-    for (const PpTile &t : pw ? PP_F16_1X1 : PP_F16)
-        if (t.bn == bn && (M + t.bm - 1) / t.bm * (a.N / bn) >= t.tiles) return &t;
-    return nullptr;
+    const long M = (long)a.nimg * a.P * a.Q, n64 = (a.N + 63) / 64, n128 = (a.N + 127) / 128;
+    // (fp16) 128 x 128 tiles on a channel count that does not fill them
+    const bool big = n64 % 2 && n128 * 90 <= n64 * 64 && (M + 127) / 128 * n128 >= 384;
+    const bool rag = a.Cs % ks || a.N % 64 || (ks == 64 && !pw && big);
+    if (rag && (a.Cs < ks || a.N <= 32 || a.N % (ks / 8))) return nullptr;
+    if (dt == DT_F32) {
+        const PpTile *t = rag ? PPR_F32 : PP_F32;
+        const bool shortk = a.R * a.S * a.Cs <= 640;
+        return &t[!shortk || (M + 63) / 64 * n64 < t[0].tiles];
+    }
+    const int bn = n64 % 2 == 0 || (rag && big) ? 128 : 64;
+    if (pw && (rag ? a.Cs < 160 && (M + 127) / 128 * n128 >= 384
+                   : bn == 64 && a.N > 64 && (M + 95) / 96 * n64 > 768))
+        return nullptr;
+    auto pick = [&](auto &tab) -> const PpTile * {
+        for (const PpTile &t : tab)
+            if (t.bn == bn && (M + t.bm - 1) / t.bm * ((a.N + bn - 1) / bn) >= t.tiles) return &t;
+        return nullptr;
+    };
+    if (rag) return pw ? pick(PPR_F16_1X1) : pick(PPR_F16);
+    return pw ? pick(PP_F16_1X1) : pick(PP_F16);
 }
 
 // Whether a layer that select_conv gives to `c` runs on conv_lat at this

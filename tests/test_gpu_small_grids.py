@@ -90,6 +90,7 @@ def test_small_batches_give_the_bits_of_large_ones(case):
 # dtype, C, H, W, K, kernel, stride, residual, images, tile; ragged last pixel
 # tiles, one or several channel tiles, 1 (fewer than the stages) to 36 steps
 D3 = "conv_dma<_Float16, %d, %d, 2, 2, 3, true, 0, false, 0>"
+D4 = D3.replace("2, 3", "2, 4")
 TILES = [
     ("f16", 64, 25, 27, 128, 3, 1, True, 6, "conv_pp<128, 32, 0, false>"),
     ("f16", 64, 27, 25, 128, 1, 2, False, 40, "conv_pp<128, 32, 0, false>"),
@@ -110,6 +111,24 @@ TILES = [
     ("f16", 320, 13, 13, 192, 1, 1, True, 80, D3 % (96, 64)),
     ("f16", 384, 13, 13, 64, 1, 1, False, 70, D3 % (64, 64)),
     ("f16", 192, 13, 13, 64, 1, 1, True, 40, D3 % (32, 64)),
+    # channels that end within a step, channel tiles that end within a tile
+    ("f16", 72, 25, 27, 136, 3, 1, True, 5, "conv_ppr<_Float16, 64, 32>"),
+    ("f16", 104, 25, 27, 40, 3, 2, False, 60, "conv_ppr<_Float16, 64, 64>"),
+    ("f16", 72, 31, 29, 40, 3, 1, True, 50, "conv_ppr<_Float16, 64, 96>"),
+    ("f16", 72, 27, 25, 120, 3, 1, False, 5, "conv_ppr<_Float16, 128, 32>"),
+    ("f16", 136, 27, 25, 232, 3, 1, True, 10, "conv_ppr<_Float16, 128, 64>"),
+    ("f16", 72, 57, 53, 136, 3, 1, True, 9, "conv_ppr<_Float16, 128, 128>"),
+    ("f16", 128, 27, 25, 192, 3, 1, False, 40, "conv_ppr<_Float16, 128, 128>"),
+    ("f16", 64, 27, 25, 168, 5, 2, True, 18, "conv_ppr<_Float16, 64, 32>"),
+    ("f16", 200, 13, 13, 232, 1, 1, True, 13, D4 % (32, 128)),
+    ("f16", 264, 13, 13, 96, 1, 1, False, 70, D4 % (64, 128)),
+    ("f16", 192, 13, 13, 232, 1, 1, True, 160, D4 % (128, 128)),
+    ("f16", 328, 13, 13, 136, 1, 1, True, 12, D4 % (32, 64)),
+    ("f16", 576, 13, 13, 160, 1, 1, False, 25, D4 % (64, 64)),
+    ("f16", 168, 13, 13, 160, 1, 1, True, 80, D4 % (96, 64)),
+    ("f32", 36, 27, 25, 100, 3, 1, True, 9, "conv_ppr<float, 64, 32>"),
+    ("f32", 44, 27, 25, 132, 3, 2, False, 60, "conv_ppr<float, 64, 32>"),
+    ("f32", 36, 49, 51, 36, 3, 1, True, 40, "conv_ppr<float, 64, 64>"),
     ("f32", 96, 27, 25, 64, 3, 1, True, 13, "conv_pp32<64, 32>"),
     ("f32", 96, 27, 25, 128, 1, 2, False, 90, "conv_pp32<64, 32>"),
     ("f32", 128, 13, 15, 192, 3, 1, False, 20, "conv_pp32<64, 32>"),

@@ -37,7 +37,7 @@ def code(tmp_path_factory):
         m = re.match(r"[0-9a-f]+ <(.*)>:$", line)
         if m:
             cur = fns.setdefault(m.group(1), []) \
-                if re.search("conv_pp|conv_dma.*Li2ELi2E(Li3E|Li2ELb1ELi16ELb1ELi0E)",
+                if re.search("conv_pp|conv_dma.*Li2ELi2E(Li[34]E|Li2ELb1ELi16ELb1ELi0E)",
                              m.group(1)) else None
         elif cur is not None and line.startswith("\t"):
             cur.append(line.split("//")[0].strip())
