@@ -1682,13 +1682,13 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// fp16 implicit-GEMM convolution for the widest layers (>= 64 input
-// channels, output channels in tiles of BN = 256).  Same GEMM view, operand
-// roles, LDS-DMA staging and row swizzle as conv_dma, for a BM-pixel x
-// BN-channel tile and K steps of 64 halves; one workgroup a CU, four waves
-// of BM / 2 pixels x 128 channels.  What bounds it on these layers is the
-// matrix core (and the power it draws) as long as nothing stalls its one
-// wave per SIMD, so:
+// Implicit-GEMM convolution with inline MFMAs (conv_pp fp16, conv_pp32 fp32;
+// conv_ppr, RAG, where channels end within a step or a tile).  Same GEMM view,
+// operand roles, LDS-DMA staging and row swizzle as conv_dma, for a BM-pixel
+// x BN-channel tile and K steps of 128 bytes, four waves of half the pixels
+// by half the channels.  With the largest tiles, 256 channels x 224 pixels
+// and one workgroup a CU, what bounds it is the matrix core (and the power it
+// draws) as long as nothing stalls its one wave per SIMD, so:
 //  - large wave tiles: 15 fragment reads feed 56 MFMAs; with eight waves of
 //    64 channels they were 23 per 56, and the LDS, which also takes the
 //    DMAs, was the busier unit;
