@@ -5615,8 +5615,19 @@ __global__ __launch_bounds__(256) void gap_k(const T *x, T *y, int nimg,
     const int c = blockIdx.y * 64 + lane;
     const T *xp = x + (size_t)img * HW * C;
     float acc = 0.f;
+    // sixteen pixels in flight: one at a time the 13 of a 7x7 map's quarter
+    // took their latency one after another (1280 channels of 128 images 9.5
+    // -> 4.8 us).  Pixels past the map add +0, which no sum that starts at +0
+    // can tell.
     if (c < C)
-        for (int i = q; i < HW; i += 4) acc += to_f(xp[(size_t)i * C + c]);
+        for (int i = q; i < HW; i += 64) {
+            T v[16];
+#pragma unroll
+            for (int k = 0; k < 16; k++)
+                v[k] = xp[(size_t)(i + 4 * k < HW ? i + 4 * k : i) * C + c];
+#pragma unroll
+            for (int k = 0; k < 16; k++) acc += i + 4 * k < HW ? to_f(v[k]) : 0.f;
+        }
     part[q][lane] = acc;
     __syncthreads();
     if (q == 0 && c < C) {

@@ -292,3 +292,28 @@ def test_filters_in_registers_give_the_bits_of_one_image(case):
     err = (y.cpu().float() - ref).flatten(2).norm(dim=2)
     # every row of every image: one rounding to 11 bits
     assert bool((err <= 2.0 ** -11 * ref.flatten(2).norm(dim=2)).all())
+
+
+@pytest.mark.parametrize("hw", [1, 3, 8, 9, 12])
+def test_global_pool_over_part_and_whole_batches_of_pixels(hw):
+    """Global average pools of maps that end within, at and past the sixteen
+    pixels that a lane loads together."""
+    import paper_2609_16742_amd as P
+    import oracle
+    from test_gpu_parity import _check_outputs, _net, _oracle_rows
+    from workloads import gen
+    from workloads.nets import Net, _B
+    print("gap", hw, flush=True)
+    b = _B()
+    t = b.conv(0, 3, 32, 3, 2, 1)
+    t = b.conv(t, 32, 584, 1, 1, 0)
+    t = b.gap(t)
+    b.fc(t, 584, 10, final=True)
+    net = Net("gap%d" % hw, (3, 2 * hw, 2 * hw), b.layers, 10, "f16", 3)
+    params = gen.make_params(net, seed=hw)
+    cn = _net(P, net, params, max_batch=3)
+    assert P.ctc.ctc_net_op_kernel(cn.h, 2, 3).startswith("gap_k")
+    xh = gen.make_inputs(net, 3, seed=hw)
+    y = cn.forward(torch.from_numpy(xh).cuda()).cpu().numpy()
+    _check_outputs(y, _oracle_rows(net, oracle.protect_params(net, params), xh,
+                                   [0, 1, 2]), net.dtype)
