@@ -173,9 +173,11 @@ ctc_status ctc_conv2d_workspace_bytes(const ctc_layer_desc *desc,
                                       int32_t w, int32_t pool, size_t *bytes);
 
 /* Name of the kernel ctc_conv2d_forward launches for this conv (as
- * rocprofv3 lists it) without a workspace, copied into name[cap]; with a
- * workspace of ctc_conv2d_workspace_bytes a split layer also launches
- * splitk_reduce (or, in calls of a few images, splits inside one kernel).
+ * rocprofv3 lists it) without a workspace or a residual, copied into
+ * name[cap].  With a workspace of ctc_conv2d_workspace_bytes a split layer
+ * also launches splitk_reduce (or, in calls of a few images, splits inside
+ * one kernel); with a residual a pooled layer of 64 input channels may run
+ * another instance of its kernel.
  * Host, synchronous.  Errors: as ctc_conv2d_forward's argument checks. */
 ctc_status ctc_conv2d_kernel_name(const ctc_layer_desc *desc, ctc_dtype dtype,
                                   int32_t n, int32_t h, int32_t w, int32_t pool,

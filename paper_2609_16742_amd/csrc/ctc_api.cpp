@@ -2617,6 +2617,7 @@ ctc_status ctc_net_op_kernel(const ctc_net *net, int32_t i, int32_t nimg,
         pa.H = ti.h; pa.W = ti.w; pa.P = to.h; pa.Q = to.w;
         pa.R = co.k; pa.S = co.k; pa.stride = co.stride; pa.pad = co.pad;
         pa.pool = 2;
+        pa.res = co.residual >= 0 ? (const void *)1 : nullptr;  // naming only
         conv_pool = conv_pool_ok(dt, pa);
     }
     if (conv_pool) {

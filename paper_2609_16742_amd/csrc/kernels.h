@@ -166,8 +166,8 @@ long down_tiles(const DownArgs &a);           // workgroups of a launch
 const char *down_kernel_name(const DownArgs &a);
 hipError_t launch_down(const DownArgs &a, hipStream_t st);
 
-// Name of the kernel launch_conv runs for these args (a.part null or not as
-// in the launch: only its presence counts).
+// Name of the kernel launch_conv runs for these args (a.part and a.res null
+// or not as in the launch: only their presence counts).
 const char *conv_kernel_name(int dt, const ConvArgs &a);
 // Depthwise convolution (direct, no MFMA).
 // MobileNetV2-type inverted residual block as one kernel: expand 1x1 (+BN,

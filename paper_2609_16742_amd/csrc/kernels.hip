@@ -1123,7 +1123,10 @@ static hipError_t run_img(const ConvArgs &a, hipStream_t st) {
 constexpr int ROWS_RING = 6, ROWS_SLOT = 3072;   // rows in flight; 24 pixels
 constexpr int ROWS_LDS = 4 * ROWS_RING * ROWS_SLOT + 512;
 
-template <bool POOL, bool WIDE>
+// RES: with the pool, whether there is a residual (without it a.res says so):
+// it is added to each of a window's four pixels before their ReLU and
+// rounding, and its registers stay out of the form without one.
+template <bool POOL, bool WIDE, bool RES = false>
 __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
     constexpr int RING = ROWS_RING * ROWS_SLOT, SC = 4 * RING;
     static_assert(RING == 16 * 9 * 128, "16 channels' filters fill a ring");
@@ -1238,9 +1241,17 @@ __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
         in = rd;
     }
     in_lane(in);
-    int ylane = out_lane(rd), rlane = ylane;
+    // this lane's residual offset in a row of the map (unpooled: as in out_lane)
+    const bool has_res = POOL ? RES : a.res != nullptr;
+    const int rrow = a.Q * a.N * 2;
+    auto res_lane = [&](const Place &p) {
+        const int x = p.x0 + fr;
+        return x < a.Q && nl < a.N ? (x * a.N + nl) * 2 : OOB;
+    };
+    int ylane = out_lane(rd), rlane = res_lane(rd);
     char *ring = lds + wave * RING;
     const int xsize = a.nimg * a.H * xrow, ysize = a.nimg * U * yrow;
+    const int rsize = a.nimg * a.P * rrow;
     f16x8 rv[ROWS_RING];                         // residual rows of the slots
     // row in.k of the stream into a slot (past the map or the end: zeros, by
     // an empty buffer); pixel px of the slot holds column x0 - 1 + px, its
@@ -1252,16 +1263,17 @@ __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
         const int soff = ok ? in.xoff : 0;
 #pragma unroll
         for (int d = 0; d < 3; d++) dma16(r, ring + slot * ROWS_SLOT + d * 1024, xlane[d], soff);
-        if (!POOL && a.res) {
+        if (has_res) {
             const bool rok = (in.rows > 0) & (in.k >= 2);
-            rv[slot] = get(make_rsrc(a.res, rok ? ysize : 0), rlane,
-                           rok ? in.yoff + (in.k - 2) * yrow : 0);
+            const int roff = POOL ? (in.img * a.P + in.y0 + in.k - 2) * rrow
+                                  : in.yoff + (in.k - 2) * yrow;
+            rv[slot] = get(make_rsrc(a.res, rok ? rsize : 0), rlane, rok ? roff : 0);
         }
         in.xoff += xrow;
         if (++in.k == in.rows + 2) {
             next_segment(in);
             in_lane(in);
-            rlane = out_lane(in);
+            rlane = res_lane(in);
         }
     };
     int fo[3][2];                                // fragment offsets in a slot
@@ -1319,7 +1331,7 @@ __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
 #pragma unroll
             for (int e = 0; e < 4; e++) v[i * 4 + e] = t[e];
         }
-        if (!POOL && a.res) {
+        if (has_res) {
 #pragma unroll
             for (int e = 0; e < 8; e++) v[e] += (float)rv[u][e];
         }
@@ -1402,11 +1414,19 @@ __global__ __launch_bounds__(256, 2) void conv_rows4(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
     rows_body<POOL, false>(a, lds);
 }
+template <bool WIDE>
+__global__ __launch_bounds__(256, 2) void conv_rows_pool_res(ConvArgs a) {
+    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
+    rows_body<true, WIDE, true>(a, lds);
+}
 template <bool POOL>
 static hipError_t run_rows(const ConvArgs &a, hipStream_t st) {
     const int nb = (a.N + 63) / 64;
     const dim3 grid((unsigned)(8 * (64 / nb * nb)));
-    if (a.N % 8)
+    if (POOL && a.res)
+        launch(a.N % 8 ? conv_rows_pool_res<false> : conv_rows_pool_res<true>, grid, dim3(256),
+               st, a);
+    else if (a.N % 8)
         launch(conv_rows4<POOL>, grid, dim3(256), st, a);
     else
         launch(conv_dma<_Float16, 128, POOL ? 64 : 128, 2, 2, 2, true, 16, POOL, 1>, grid,
@@ -3194,7 +3214,9 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
     case H_128x64: return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, false, 1>";
     case ROWS: if (a.N % 8) return "conv_rows4<false>";
                return "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>";
-    case ROWS_P: if (a.N % 8) return "conv_rows4<true>";
+    case ROWS_P: if (a.res) return a.N % 8 ? "conv_rows_pool_res<false>"
+                                           : "conv_rows_pool_res<true>";
+                 if (a.N % 8) return "conv_rows4<true>";
                  return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>";
     default: return f ? "conv_dma<float, 128, 128, 2, 2, 2, true, 0, false, 0>"
                       : "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 0, false, 0>";

@@ -217,15 +217,17 @@ POOLED = [
     (9, 60, 60, 64, 64), (28, 47, 47, 64, 64), (5, 131, 45, 64, 64), (1, 182, 257, 64, 64),
     (9, 60, 60, 64, 40), (9, 60, 60, 64, 36), (9, 60, 60, 64, 24), (8, 64, 96, 128, 128), (30, 38, 47, 192, 128),
     (15, 39, 93, 96, 128), (30, 28, 56, 128, 256), (40, 42, 30, 128, 256),
+    (4, 96, 112, 32, 64), (8, 64, 96, 72, 128),
 ]
 
 
+@pytest.mark.parametrize("residual", [False, True])
 @pytest.mark.parametrize("case", POOLED)
-def test_fused_pool_gives_the_bits_of_the_pooled_convolution(case):
+def test_fused_pool_gives_the_bits_of_the_pooled_convolution(case, residual):
     import paper_2609_16742_amd as P
     ctc = P.ctc
     n, H, W, C, K = case
-    print("pooled", case, flush=True)
+    print("pooled", case, "residual", residual, flush=True)
     g = torch.Generator(device="cuda")
     g.manual_seed(POOLED.index(case))
     d = ctc.layer_desc(C, K, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
@@ -234,17 +236,53 @@ def test_fused_pool_gives_the_bits_of_the_pooled_convolution(case):
     scale = torch.rand(K, device="cuda", generator=g) + 0.5
     shift = torch.randn(K, device="cuda", generator=g)
     x[0, H // 2, W // 2, 3] = float("inf")
+    r = torch.randn((n, H, W, K), device="cuda", generator=g).half() if residual else None
     for relu in (0, 1):
         y = torch.full((n, H, W, K), float("nan"), device="cuda").half()
         yp = torch.full((n, H // 2, W // 2, K), 7.0, device="cuda").half()
-        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, None, relu, y)
-        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, None, relu, yp,
+        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, r, relu, y)
+        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, n, H, W, x, w, scale, shift, r, relu, yp,
                                pool=2)
         win = y[:, :H // 2 * 2, :W // 2 * 2].unflatten(1, (-1, 2)).unflatten(3, (-1, 2))
         ref = win.float().amax(dim=(2, 4)).half()      # amax keeps a NaN
         assert torch.equal(torch.isnan(ref), torch.isnan(yp))
         ok = ~torch.isnan(ref)
         assert torch.equal(ref[ok], yp[ok])
+
+
+@pytest.mark.parametrize("C,H,W", [(64, 60, 60), (64, 45, 77), (128, 64, 96), (256, 56, 28)])
+def test_residual_conv_with_a_fused_pool_in_a_network(C, H, W):
+    """A residual block whose output only feeds a 2x2 pool: the pool runs in
+    the kernel of the block's second conv, with the bits of the separate
+    kernels."""
+    import paper_2609_16742_amd as P
+    import oracle
+    from test_gpu_parity import _check_outputs, _net, _oracle_rows
+    from workloads import gen
+    from workloads.nets import Net, _B, _basic_block
+    print("residual + pool", C, H, W, flush=True)
+    b = _B()
+    t = b.conv(0, 3, C, 3, 1, 1)
+    t = _basic_block(b, t, C, C, 1)
+    pool = b.maxpool(t, 2, 2, 0)
+    b.fc(b.gap(pool), C, 10, final=True)
+    n = 30 if C == 256 else 9
+    net = Net("respool%d" % C, (3, H, W), b.layers, 10, "f16", n)
+    params = gen.make_params(net, seed=C)
+    cn = _net(P, net, params, max_batch=n)
+    names = [P.ctc.ctc_net_op_kernel(cn.h, i, n) for i in (pool - 2, pool - 1)]
+    assert names[0] == names[1], names              # the conv and its pool
+    x = torch.from_numpy(gen.make_inputs(net, n, seed=C)).cuda()
+    on = cn.forward(x).cpu().numpy()
+    pooled = cn.tensor(pool, n).cpu().numpy().copy()
+    cn.set_fusion(P.ctc.CTC_FUSE_BLOCK | P.ctc.CTC_FUSE_STEM)
+    off = cn.forward(x).cpu().numpy()
+    apart = cn.tensor(pool, n).cpu().numpy()
+    same = bool((pooled.view(np.uint16) == apart.view(np.uint16)).all())
+    assert same and np.array_equal(on.view(np.uint32), off.view(np.uint32))
+    rows = [0, n - 1]
+    _check_outputs(on[rows], _oracle_rows(net, oracle.protect_params(net, params),
+                                          x.cpu().numpy(), rows), net.dtype)
 
 
 # n, H, W, K, residual: layers of 64 input channels with filters in registers
