@@ -552,11 +552,12 @@ __device__ __forceinline__ void dma_epilogue(const ConvArgs &a,
         }
     }
 }
-// conv_pp's addressing: 31-bit byte offsets and input coordinates (past the
-// pads too) in 16 bits
+// conv_pp's addressing: 31-bit byte offsets, and the input coordinates of a
+// window's first tap, -pad to size + pad - 1 at most, in 16 bits (-16384,
+// which all taps leave negative, marks rows past the map)
 __host__ __device__ static inline bool pp_addr_ok(const ConvArgs &a, int es) {
-    return a.H < 16384 && a.W < 16384 && a.R < 8192 && a.S < 8192 &&
-           a.pad < 8192 && (long)a.nimg * a.H * a.W * a.Cs * es < (1l << 31) &&
+    return (long)a.H + a.pad <= 32768 && (long)a.W + a.pad <= 32768 && a.R < 8192 &&
+           a.S < 8192 && a.pad < 8192 && (long)a.nimg * a.H * a.W * a.Cs * es < (1l << 31) &&
            (long)a.N * a.R * a.S * a.Cs * es < (1l << 31);
 }
 
@@ -2900,7 +2901,8 @@ enum ConvCfg {
 static bool pp_fits(const ConvArgs &a) {
     const long M = (long)a.nimg * a.P * a.Q;
     const long t = (M + 223) / 224 * (a.N / 256), t128 = (M + 127) / 128 * (a.N / 128);
-    return a.R == 3 && a.S == 3 && a.Cs % 64 == 0 && a.N % 256 == 0 && pp_addr_ok(a, 2) &&
+    return a.R == 3 && a.S == 3 && a.Cs % 64 == 0 && a.N % 256 == 0 &&
+           (long)a.N * 9 * a.Cs * 2 < (1l << 31) &&
            (a.pool ? t >= 192 : (t128 + 255) / 256 >= 3 * ((t + 255) / 256));
 }
 
@@ -2990,11 +2992,15 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         if (a.N < 64) return H_128x64;
     }
     if (dt == DT_F16 && pp_fits(a)) {
-        if (!a.pool) return PP_256;
+        // (longer maps than conv_pp can address: conv_dma, whose pooled tile
+        // then takes the layers that would pool here)
+        const bool pp = pp_addr_ok(a, 2);
+        if (!a.pool && pp) return PP_256;
         // the tile width with fewer tiles (ties: 8)
         const long t8 = pool_tiles(a, 28, 8), t16 = pool_tiles(a, 14, 16);
-        if (t8 <= t16 && pool_waste_ok(a, 28, 8)) return PP_256_P8;
-        if (pool_waste_ok(a, 14, 16)) return PP_256_P16;
+        if (a.pool && t8 <= t16 && pool_waste_ok(a, 28, 8))
+            return pp ? PP_256_P8 : D_128x128_P16;
+        if (a.pool && pool_waste_ok(a, 14, 16)) return pp ? PP_256_P16 : D_128x128_P16;
     }
     if (a.N <= 32) return D_64x32;
     // fp32 MFMA work per K step is 8x the fp16 one: small tiles keep more

@@ -182,16 +182,19 @@ def test_tiles_of_every_size_give_the_bits_of_one_image(case):
                  * ref.flatten(1).norm(dim=1)).all())
 
 
-# maps taller or wider than the 16-bit coordinates of conv_pp's tiles
-@pytest.mark.parametrize("dtype,H,W,K", [("f16", 33001, 2, 64), ("f16", 2, 33001, 256),
-                                         ("f32", 2, 16500, 64), ("f32", 33001, 2, 64)])
-def test_long_maps_keep_their_kernel(dtype, H, W, K):
+# maps taller or wider than the 16-bit coordinates of conv_pp's tiles, and the
+# largest that fit (size + pad = 32768)
+@pytest.mark.parametrize("dtype,H,W,K,pp", [
+    ("f16", 33001, 2, 64, False), ("f16", 2, 33001, 256, False), ("f32", 2, 16500, 64, True),
+    ("f32", 33001, 2, 64, False), ("f16", 2, 32767, 512, True), ("f16", 32767, 4, 512, True),
+    ("f16", 4, 32768, 512, False), ("f32", 2, 32767, 64, True), ("f32", 2, 32768, 64, False)])
+def test_long_maps_keep_their_kernel(dtype, H, W, K, pp):
     import paper_2609_16742_amd as P
     ctc = P.ctc
     print("long map", dtype, H, W, K, flush=True)
     d = ctc.layer_desc(64, K, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
     dt = ctc.DTYPES[dtype]
-    assert "conv_pp" not in ctc.ctc_conv2d_kernel_name(d, dt, 1, H, W)
+    assert ("conv_pp" in ctc.ctc_conv2d_kernel_name(d, dt, 1, H, W)) == pp
     tdt = torch.float16 if dtype == "f16" else torch.float32
     g = torch.Generator(device="cuda")
     g.manual_seed(K)
@@ -208,6 +211,29 @@ def test_long_maps_keep_their_kernel(dtype, H, W, K):
     ref, got = (ref[:, 1:], y[:, -19:]) if H > 20 else (ref[:, :, 1:], y[:, :, -19:])
     err = (got.cpu().double() - ref).norm()
     assert err <= (2.0 ** -11 if dtype == "f16" else 1e-5) * ref.norm()
+
+
+# pooled layers of 256-channel tiles on maps up to and past conv_pp's coordinates
+@pytest.mark.parametrize("H,W,pp", [(14, 16400, True), (14, 32767, True), (14, 32768, False),
+                                    (33600, 8, False)])
+def test_long_maps_keep_their_fused_pool(H, W, pp):
+    import paper_2609_16742_amd as P
+    ctc = P.ctc
+    print("long map, pooled", H, W, flush=True)
+    d = ctc.layer_desc(64, 256, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
+    assert ("conv_pp" in ctc.ctc_conv2d_kernel_name(d, ctc.CTC_F16, 1, H, W, 2)) == pp
+    g = torch.Generator(device="cuda")
+    g.manual_seed(W)
+    x = torch.randn((1, H, W, 64), device="cuda", generator=g).half()
+    w = (torch.randn((256, 3, 3, 64), device="cuda", generator=g) / 24).half()
+    scale, shift = (torch.rand(256, device="cuda", generator=g) for _ in range(2))
+    y = torch.full((1, H, W, 256), float("nan"), device="cuda").half()
+    yp = torch.full((1, H // 2, W // 2, 256), float("nan"), device="cuda").half()
+    for pool, out in ((0, y), (2, yp)):
+        ctc.ctc_conv2d_forward(d, ctc.CTC_F16, 1, H, W, x, w, scale, shift, None, 1, out,
+                               pool=pool)
+    win = y[:, :H // 2 * 2, :W // 2 * 2].unflatten(1, (-1, 2)).unflatten(3, (-1, 2))
+    assert bool((win.amax(dim=(2, 4)) == yp).all())
 
 
 # n, H, W, C, K: conv and 2x2 pool in one kernel; odd maps, strips of 16
