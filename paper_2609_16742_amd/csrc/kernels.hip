@@ -1139,7 +1139,6 @@ __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
     const int nb = (a.N + 63) / 64, per = (int)gridDim.x >> 3;
     const int lb = (int)(blockIdx.x & 7) * per + (int)(blockIdx.x >> 3);
     const int cb = lb % nb * 64, g = wave & 1;
-    const Rsrc xr = make_rsrc(a.x, (long)a.nimg * a.H * a.W * 128);
     const Rsrc wr = make_rsrc(a.w, (long)a.N * 1152);
 
     // the filters of MFMA rows m of (channel half g, i) through ring 2 g + i
@@ -5107,9 +5106,15 @@ hipError_t launch_dwpw(const DwPwArgs &a, hipStream_t st) {
 // ReLU of values rounded to fp16, for intermediates that only enter products:
 // one packed IEEE maximum per two values (a NaN stays one) where the rounded
 // comparison and selection in fp32 take two instructions each.  It makes +0
-// of -0, which no sum of products that starts at +0 can tell apart.
+// of -0, which no sum of products that starts at +0 can tell apart.  The
+// values are rounded to fp32 first, as in the separate kernels: the empty
+// asm keeps the compiler from folding a multiply-add and the conversion into
+// v_fma_mixlo_f16, which rounds once (a test looks for it in the built code).
 __device__ __forceinline__ f16x4 relu_h4(f32x4 v) {
-    return __builtin_elementwise_maximum(__builtin_convertvector(v, f16x4), (f16x4)(0));
+    float v0 = v[0], v1 = v[1], v2 = v[2], v3 = v[3];
+    asm("" : "+v"(v0), "+v"(v1), "+v"(v2), "+v"(v3));
+    const f16x4 o = {(_Float16)v0, (_Float16)v1, (_Float16)v2, (_Float16)v3};
+    return __builtin_elementwise_maximum(o, (f16x4)(0));
 }
 __device__ __forceinline__ f16x8 bn_relu_h8(const float (&s)[8], f32x4 sa, f32x4 sb, f32x4 ha,
                                             f32x4 hb) {
@@ -5117,7 +5122,7 @@ __device__ __forceinline__ f16x8 bn_relu_h8(const float (&s)[8], f32x4 sa, f32x4
 #pragma unroll
     for (int k = 0; k < 8; k++) {
         float t = s[k] * (k < 4 ? sa : sb)[k & 3] + (k < 4 ? ha : hb)[k & 3];
-        asm("" : "+v"(t));                       // (no v_fma_mixlo_f16: it rounds once)
+        asm("" : "+v"(t));                       // (as in relu_h4)
         o[k] = (_Float16)t;
     }
     return __builtin_elementwise_maximum(o, (f16x8)(0));
@@ -5283,9 +5288,11 @@ __global__ __launch_bounds__(256, ir_wgs(ST, CP, COW, EC)) void conv_ir(IrArgs a
             }
         } else if (EC == 32 && ecnt > 16) {
             // a full 32-channel chunk: two groups of 16, each over half the
-            // halo tiles
+            // halo tiles (a constant trip count: the asm in relu_h4 keeps the
+            // compiler from unrolling loops with another)
 #pragma unroll 2
-            for (int t = wave >> 1; t < NH16; t += 2) expand_tile(t, wave & 1);
+            for (int u = 0; u < NH16 / 2; u++) expand_tile(u * 2 + (wave >> 1), wave & 1);
+            if (NH16 % 2 && wave < 2) expand_tile(NH16 - 1, wave);
         } else {
             // a short last chunk: its one or two channel groups split the
             // halo tiles across the four waves

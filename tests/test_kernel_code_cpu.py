@@ -19,8 +19,8 @@ AGPR = re.compile(r"\ba(\d+|\[\d+:\d+\])")
 
 
 @pytest.fixture(scope="module")
-def code(tmp_path_factory):
-    """Instructions per kernel with such MFMAs of libctc.so, in address order."""
+def kernels(tmp_path_factory):
+    """Instructions per kernel of libctc.so, in address order."""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     d = tmp_path_factory.mktemp("code")
@@ -36,12 +36,27 @@ def code(tmp_path_factory):
     for line in out.splitlines():
         m = re.match(r"[0-9a-f]+ <(.*)>:$", line)
         if m:
-            cur = fns.setdefault(m.group(1), []) \
-                if re.search("conv_pp|conv_dma.*Li2ELi2E(Li[34]E|Li2ELb1ELi16ELb1ELi0E)",
-                             m.group(1)) else None
+            cur = fns.setdefault(m.group(1), [])
         elif cur is not None and line.startswith("\t"):
             cur.append(line.split("//")[0].strip())
     return fns
+
+
+@pytest.fixture(scope="module")
+def code(kernels):
+    """The kernels with such MFMAs."""
+    return {n: ins for n, ins in kernels.items()
+            if re.search("conv_pp|conv_dma.*Li2ELi2E(Li[34]E|Li2ELb1ELi16ELb1ELi0E)", n)}
+
+
+def test_results_are_rounded_to_fp32_before_fp16(kernels):
+    """v_fma_mixlo_f16 / mixhi round a multiply-add once, straight to fp16:
+    the fused and the separate kernels only agree bit for bit if none uses
+    them for its scale and shift."""
+    assert any("conv_ir" in n for n in kernels) and any("conv_dma" in n for n in kernels)
+    once = {n: s for n, ins in kernels.items() for s in ins
+            if s.startswith(("v_fma_mixlo", "v_fma_mixhi"))}
+    assert not once, once
 
 
 def test_accumulators_of_inline_mfmas_are_touched_only_at_a_distance(code):
