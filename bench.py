@@ -517,7 +517,7 @@ def gemm_reference(net, B, names, launches, ms, reps=20):
     for i, L in enumerate(net.layers):
         n_l = int(launches[1 + i])
         if (L["op"] != "conv" or L["groups"] != 1 or n_l == 0 or
-                not names[i].startswith(("conv_pp", "conv_dma", "conv_img"))):
+                not names[i].startswith(("conv_pp", "conv_dma", "conv_img", "conv_rows"))):
             continue
         c, p, q = shp[i + 1]
         M, K, N = B * p * q, L["c_in"] * L["k"] * L["k"], c

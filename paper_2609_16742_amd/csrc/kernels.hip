@@ -552,24 +552,6 @@ __device__ __forceinline__ void dma_epilogue(const ConvArgs &a,
         }
     }
 }
-// conv_pp's addressing: 31-bit byte offsets, and the input coordinates of a
-// window's first tap, -pad to size + pad - 1 at most, in 16 bits (-16384,
-// which all taps leave negative, marks rows past the map)
-__host__ __device__ static inline bool pp_addr_ok(const ConvArgs &a, int es) {
-    return (long)a.H + a.pad <= 32768 && (long)a.W + a.pad <= 32768 && a.R < 8192 &&
-           a.S < 8192 && a.pad < 8192 && (long)a.nimg * a.H * a.W * a.Cs * es < (1l << 31) &&
-           (long)a.N * a.R * a.S * a.Cs * es < (1l << 31);
-}
-
-// conv_pp's body (below), and the LDS it needs
-template <typename T, int BN, int BM>
-constexpr int pp_lds() {
-    constexpr int MAIN = (3 * BM + 2 * BN) * 128, EPI = BM * (BN * (int)sizeof(T) + 16);
-    return MAIN > EPI ? MAIN : EPI;
-}
-template <typename T, int BN, int BM, int TW, bool POOL, bool RAG = false>
-__device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds);
-
 template <typename T, int BM, int BN, int WM, int WN, int NS, bool XCD,
           int TW = 0, bool POOL = false, int HALO = 0>
 __global__ __launch_bounds__(64 * WM * WN) void conv_dma(ConvArgs a) {
@@ -604,20 +586,9 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_dma(ConvArgs a) {
     // epilogue rows staged per pass: all of them when that fits in 150 KB
     constexpr int EPR = BM * EROW * 4 <= 153600 ? BM : BM / 2;
     static_assert(EPR * EROW * 4 <= 153600 && EPR % 16 == 0 && TM % 16 == 0, "epi");
-    constexpr int LDS_DMA = HBYTES + NS * STAGE > EPR * EROW * 4 ? HBYTES + NS * STAGE
-                                                                 : EPR * EROW * 4;
-    // The pooled 128 x 128 tile runs conv_pp's loop on layers that it can
-    // address (VGG-16 conv2_2 at batch 32: 199 -> 154 us)
-    constexpr bool PP = ES == 2 && POOL && HALO == 0 && BM == 128 && BN == 128 && WM == 2 &&
-                        WN == 2;
-    constexpr int LDS_PP = PP ? pp_lds<T, BN, BM>() : 0;
-    __shared__ __attribute__((aligned(16))) char lds[LDS_DMA > LDS_PP ? LDS_DMA : LDS_PP];
-    if constexpr (PP) {
-        if (pp_addr_ok(a, ES) && a.Cs % KS == 0 && a.N % BN == 0) {
-            pp_body<T, BN, BM, TW, POOL>(a, lds);
-            return;
-        }
-    }
+    constexpr int LDS_BYTES = HBYTES + NS * STAGE > EPR * EROW * 4 ? HBYTES + NS * STAGE
+                                                                   : EPR * EROW * 4;
+    __shared__ __attribute__((aligned(16))) char lds[LDS_BYTES];
 
     const int M = a.nimg * a.P * a.Q;
     int m0 = blockIdx.x * BM, n0 = blockIdx.y * BN;
@@ -1127,7 +1098,7 @@ constexpr int ROWS_LDS = 4 * ROWS_RING * ROWS_SLOT + 512;
 // RES: with the pool, whether there is a residual (without it a.res says so):
 // it is added to each of a window's four pixels before their ReLU and
 // rounding, and its registers stay out of the form without one.
-template <bool POOL, bool WIDE, bool RES = false>
+template <bool POOL, bool WIDE, bool RES>
 __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
     constexpr int RING = ROWS_RING * ROWS_SLOT, SC = 4 * RING;
     static_assert(RING == 16 * 9 * 128, "16 channels' filters fill a ring");
@@ -1396,41 +1367,17 @@ __device__ __forceinline__ void rows_body(const ConvArgs &a, char *lds) {
     wait_vmcnt<0>();                             // no DMA outlives the workgroup's LDS
 }
 
-// Under the names of conv_dma's halo form.
-template <>
-__global__ __launch_bounds__(256, 2) void conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>(
-    ConvArgs a) {
+template <bool POOL, bool WIDE, bool RES>
+__global__ __launch_bounds__(256, 2) void conv_rows(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
-    rows_body<false, true>(a, lds);
+    rows_body<POOL, WIDE, RES>(a, lds);
 }
-template <>
-__global__ __launch_bounds__(256, 2) void conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>(
-    ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
-    rows_body<true, true>(a, lds);
-}
-template <bool POOL>
-__global__ __launch_bounds__(256, 2) void conv_rows4(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
-    rows_body<POOL, false>(a, lds);
-}
-template <bool WIDE>
-__global__ __launch_bounds__(256, 2) void conv_rows_pool_res(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[ROWS_LDS];
-    rows_body<true, WIDE, true>(a, lds);
-}
-template <bool POOL>
+template <bool POOL, bool RES>
 static hipError_t run_rows(const ConvArgs &a, hipStream_t st) {
     const int nb = (a.N + 63) / 64;
     const dim3 grid((unsigned)(8 * (64 / nb * nb)));
-    if (POOL && a.res)
-        launch(a.N % 8 ? conv_rows_pool_res<false> : conv_rows_pool_res<true>, grid, dim3(256),
-               st, a);
-    else if (a.N % 8)
-        launch(conv_rows4<POOL>, grid, dim3(256), st, a);
-    else
-        launch(conv_dma<_Float16, 128, POOL ? 64 : 128, 2, 2, 2, true, 16, POOL, 1>, grid,
-               dim3(256), st, a);
+    launch(a.N % 8 ? conv_rows<POOL, false, RES> : conv_rows<POOL, true, RES>, grid, dim3(256),
+           st, a);
     return hipGetLastError();
 }
 
@@ -1754,7 +1701,22 @@ __device__ __forceinline__ void mfma_done() {
 }
 __device__ __forceinline__ void mfma_result(f32x4 &acc) { asm volatile("" : "+a"(acc)); }
 
-template <typename T, int BN, int BM, int TW, bool POOL, bool RAG>
+// conv_pp's addressing: 31-bit byte offsets, and the input coordinates of a
+// window's first tap, -pad to size + pad - 1 at most, in 16 bits (-16384,
+// which all taps leave negative, marks rows past the map)
+static bool pp_addr_ok(const ConvArgs &a, int es) {
+    return (long)a.H + a.pad <= 32768 && (long)a.W + a.pad <= 32768 && a.R < 8192 &&
+           a.S < 8192 && a.pad < 8192 && (long)a.nimg * a.H * a.W * a.Cs * es < (1l << 31) &&
+           (long)a.N * a.R * a.S * a.Cs * es < (1l << 31);
+}
+
+// The LDS of conv_pp's tiles
+template <typename T, int BN, int BM>
+constexpr int pp_lds() {
+    constexpr int MAIN = (3 * BM + 2 * BN) * 128, EPI = BM * (BN * (int)sizeof(T) + 16);
+    return MAIN > EPI ? MAIN : EPI;
+}
+template <typename T, int BN, int BM, int TW, bool POOL, bool RAG = false>
 __device__ __forceinline__ void pp_body(const ConvArgs &a, char *lds) {
     constexpr int ES = (int)sizeof(T), KS = 128 / ES;    // k per step
     typedef typename std::conditional<ES == 2, f16x8, f32x4>::type Frag;
@@ -2109,73 +2071,6 @@ __global__ __launch_bounds__(256, 1) void conv_pp32(ConvArgs a) {
     __shared__ __attribute__((aligned(16))) char lds[pp_lds<float, BN, BM>()];
     pp_body<float, BN, BM, 0, false>(a, lds);
 }
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 128, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 128>()];
-    pp_body<_Float16, 128, 128, 0, false>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 96, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 96>()];
-    pp_body<_Float16, 128, 96, 0, false>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 64>()];
-    pp_body<_Float16, 128, 64, 0, false>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 128, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 32>()];
-    pp_body<_Float16, 128, 32, 0, false>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 96, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 96>()];
-    pp_body<_Float16, 64, 96, 0, false>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 64>()];
-    pp_body<_Float16, 64, 64, 0, false>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 32>()];
-    pp_body<_Float16, 64, 32, 0, false>(a, lds);
-}
-
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 128, 128, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 128>()];
-    pp_body<_Float16, 128, 128, 0, false, true>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 128, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 64>()];
-    pp_body<_Float16, 128, 64, 0, false, true>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 128, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 128, 32>()];
-    pp_body<_Float16, 128, 32, 0, false, true>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 96, 64, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 96>()];
-    pp_body<_Float16, 64, 96, 0, false, true>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 64, 64, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 64>()];
-    pp_body<_Float16, 64, 64, 0, false, true>(a, lds);
-}
-template <>
-__global__ __launch_bounds__(256, 1) void conv_dma<_Float16, 32, 64, 2, 2, 4, true, 0, false, 0>(ConvArgs a) {
-    __shared__ __attribute__((aligned(16))) char lds[pp_lds<_Float16, 64, 32>()];
-    pp_body<_Float16, 64, 32, 0, false, true>(a, lds);
-}
-
 template <int BN, int BM, int TW, bool POOL>
 static hipError_t run_pp(const ConvArgs &a, hipStream_t st) {
     constexpr int TH = TW ? BM / TW : 1;
@@ -2197,16 +2092,6 @@ template <typename T, int BN, int BM>
 static hipError_t run_ppr(const ConvArgs &a, hipStream_t st) {
     const long tiles = ((long)a.nimg * a.P * a.Q + BM - 1) / BM * ((a.N + BN - 1) / BN);
     launch(conv_ppr<T, BN, BM>, dim3((unsigned)((tiles + 7) / 8 * 8)), dim3(256), st, a);
-    return hipGetLastError();
-}
-
-// Stride-1 1x1 layers run the same loop as conv_dma's three-stage form (NS =
-// 4: RAG).
-template <int BN, int BM, int NS = 3>
-static hipError_t run_pp1(const ConvArgs &a, hipStream_t st) {
-    const long tiles = ((long)a.nimg * a.P * a.Q + BM - 1) / BM * ((a.N + BN - 1) / BN);
-    launch(conv_dma<_Float16, BM, BN, 2, 2, NS, true>, dim3((unsigned)((tiles + 7) / 8 * 8)),
-           dim3(256), st, a);
     return hipGetLastError();
 }
 
@@ -2880,13 +2765,13 @@ hipError_t launch_stem_pool(const ConvArgs &a, int PP, int QP, hipStream_t st) {
 enum ConvCfg {
     F32_N16, F32_N32, F32_N64,
     F16V4_N32, F16V4_N64, PW_F16, STEM_F16,
-    PP_256, PP_256_P8, PP_256_P16,
+    PP_256, PP_256_P8, PP_256_P16, PP_128_P16,
     IMG_7, IMG_14,                              // conv_img on 7x7 / 14x14 maps
     IMG_7S2,                                    // conv_img, 14x14 -> 7x7 stride 2
     D_64x32, D_128x64, D_64x64, D_64x128, D_128x128, D_256x256,
     D_128x64_P16, D_128x128_P16,
     H_128x64,                                  // conv_dma with the halo A tile
-    ROWS, ROWS_P                               // rows_body
+    ROWS, ROWS_P                               // conv_rows
 };
 
 // conv_pp's 256-channel tiles on a layer: fp16 3x3 with whole 64-channel k
@@ -2929,7 +2814,7 @@ static bool halo_ok(const ConvArgs &a) {
            (long)a.N * 9 * a.Cs * 2 < (1l << 31);
 }
 
-// rows_body on a layer: whole strips of 16 columns but for a sixth of the
+// conv_rows on a layer: whole strips of 16 columns but for a sixth of the
 // work, and at least 3072 strip rows of 64 output channels (3 per wave: its
 // filters take as long as about two).  conv_pp's small tiles -> this there:
 // 56x56x64 at batch 8 7.9 -> 8.4 us, 12 9.4 -> 9.5 (2688 rows), 16 11.1 -> 10.3
@@ -2981,7 +2866,7 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         (long)a.nimg * a.H * a.W * a.Cs * 2 < (1l << 31) && (long)a.N * 9 * a.Cs * 2 < (1l << 31))
         return IMG_7S2;
     // 3x3 stride-1 layers on 64 input channels: the filters in registers
-    // (rows_body), or, for channel counts that neither it nor conv_pp's
+    // (conv_rows), or, for channel counts that neither it nor conv_pp's
     // tiles take, the halo tile (each input pixel moves to LDS once instead
     // of once per tap; with 128 input channels and with a pool on 128 output
     // channels no faster)
@@ -3021,15 +2906,17 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         if (bm128 && a.pool && pool_waste_ok(a, 8, 16)) return D_128x64_P16;
         return bm128 ? D_128x64 : D_64x64;
     }
-    if (bm128 && a.pool && pool_waste_ok(a, 8, 16)) return D_128x128_P16;
+    // (VGG-16 conv2_2 at batch 32 on conv_dma's loop 199 us, on conv_pp's 154)
+    if (bm128 && a.pool && pool_waste_ok(a, 8, 16))
+        return a.Cs % 64 == 0 && a.N % 128 == 0 && pp_addr_ok(a, 2) ? PP_128_P16 : D_128x128_P16;
     return bm128 ? D_128x128 : D_64x128;
 }
 
 static bool img_cfg(ConvCfg c) { return c == IMG_7 || c == IMG_14 || c == IMG_7S2; }
 
 static bool pool_cfg(ConvCfg c) {
-    return c == PP_256_P8 || c == PP_256_P16 || c == D_128x64_P16 || c == D_128x128_P16 ||
-           c == ROWS_P;
+    return c == PP_256_P8 || c == PP_256_P16 || c == PP_128_P16 || c == D_128x64_P16 ||
+           c == D_128x128_P16 || c == ROWS_P;
 }
 
 bool conv_pool_ok(int dt, const ConvArgs &a) {
@@ -3080,15 +2967,6 @@ static const PpTile PP_F16[] = {
     {64, 64, 160, "conv_pp<64, 64, 0, false>", run_pp<64, 64, 0, false>},
     {64, 32, 0, "conv_pp<64, 32, 0, false>", run_pp<64, 32, 0, false>},
 };
-static const PpTile PP_F16_1X1[] = {
-    {128, 128, 384, "conv_dma<_Float16, 128, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 128>},
-    {128, 96, 384, "conv_dma<_Float16, 96, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 96>},
-    {128, 64, 160, "conv_dma<_Float16, 64, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 64>},
-    {128, 32, 0, "conv_dma<_Float16, 32, 128, 2, 2, 3, true, 0, false, 0>", run_pp1<128, 32>},
-    {64, 96, 384, "conv_dma<_Float16, 96, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 96>},
-    {64, 64, 160, "conv_dma<_Float16, 64, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 64>},
-    {64, 32, 0, "conv_dma<_Float16, 32, 64, 2, 2, 3, true, 0, false, 0>", run_pp1<64, 32>},
-};
 static const PpTile PPR_F16[] = {
     {128, 128, 384, "conv_ppr<_Float16, 128, 128>", run_ppr<_Float16, 128, 128>},
     {128, 64, 160, "conv_ppr<_Float16, 128, 64>", run_ppr<_Float16, 128, 64>},
@@ -3096,14 +2974,6 @@ static const PpTile PPR_F16[] = {
     {64, 96, 384, "conv_ppr<_Float16, 64, 96>", run_ppr<_Float16, 64, 96>},
     {64, 64, 160, "conv_ppr<_Float16, 64, 64>", run_ppr<_Float16, 64, 64>},
     {64, 32, 0, "conv_ppr<_Float16, 64, 32>", run_ppr<_Float16, 64, 32>},
-};
-static const PpTile PPR_F16_1X1[] = {
-    {128, 128, 384, "conv_dma<_Float16, 128, 128, 2, 2, 4, true, 0, false, 0>", run_pp1<128, 128, 4>},
-    {128, 64, 160, "conv_dma<_Float16, 64, 128, 2, 2, 4, true, 0, false, 0>", run_pp1<128, 64, 4>},
-    {128, 32, 0, "conv_dma<_Float16, 32, 128, 2, 2, 4, true, 0, false, 0>", run_pp1<128, 32, 4>},
-    {64, 96, 384, "conv_dma<_Float16, 96, 64, 2, 2, 4, true, 0, false, 0>", run_pp1<64, 96, 4>},
-    {64, 64, 160, "conv_dma<_Float16, 64, 64, 2, 2, 4, true, 0, false, 0>", run_pp1<64, 64, 4>},
-    {64, 32, 0, "conv_dma<_Float16, 32, 64, 2, 2, 4, true, 0, false, 0>", run_pp1<64, 32, 4>},
 };
 static const PpTile PPR_F32[] = {
     {64, 64, 900, "conv_ppr<float, 64, 64>", run_ppr<float, 64, 64>},
@@ -3138,8 +3008,7 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
             if (t.bn == bn && (M + t.bm - 1) / t.bm * ((a.N + bn - 1) / bn) >= t.tiles) return &t;
         return nullptr;
     };
-    if (rag) return pw ? pick(PPR_F16_1X1) : pick(PPR_F16);
-    return pw ? pick(PP_F16_1X1) : pick(PP_F16);
+    return rag ? pick(PPR_F16) : pick(PP_F16);
 }
 
 // Whether a layer that select_conv gives to `c` runs on conv_lat at this
@@ -3160,7 +3029,7 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
 // 12.0 us at 800, 16.3 -> 22.4 at 1696).
 static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
     const int es = dt == DT_F32 ? 4 : 2;
-    if (a.pool || (c < D_64x32 && c != PW_F16 && c != PP_256 && !img_cfg(c))) return false;
+    if (a.pool || (c < D_64x32 && c != PW_F16 && !img_cfg(c))) return false;
     if (a.Cs % (16 / es) || (long)a.nimg * a.H * a.W * a.Cs * es >= (1l << 31) ||
         (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
         return false;
@@ -3199,6 +3068,7 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
     case PP_256: return "conv_pp<256, 224, 0, false>";
     case PP_256_P8: return "conv_pp<256, 224, 8, true>";
     case PP_256_P16: return "conv_pp<256, 224, 16, true>";
+    case PP_128_P16: return "conv_pp<128, 128, 16, true>";
     case IMG_7: return "conv_img<7, false, 1>";
     case IMG_14: return "conv_img<14, false, 1>";
     case IMG_7S2: return "conv_img<7, false, 2>";
@@ -3217,12 +3087,10 @@ const char *conv_kernel_name(int dt, const ConvArgs &a) {
     case D_128x128_P16: return f ? "conv_dma<float, 128, 128, 2, 2, 2, true, 16, true, 0>"
                                  : "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, true, 0>";
     case H_128x64: return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, false, 1>";
-    case ROWS: if (a.N % 8) return "conv_rows4<false>";
-               return "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>";
-    case ROWS_P: if (a.res) return a.N % 8 ? "conv_rows_pool_res<false>"
-                                           : "conv_rows_pool_res<true>";
-                 if (a.N % 8) return "conv_rows4<true>";
-                 return "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>";
+    case ROWS: return a.N % 8 ? "conv_rows<false, false, false>" : "conv_rows<false, true, false>";
+    case ROWS_P:
+        if (a.res) return a.N % 8 ? "conv_rows<true, false, true>" : "conv_rows<true, true, true>";
+        return a.N % 8 ? "conv_rows<true, false, false>" : "conv_rows<true, true, false>";
     default: return f ? "conv_dma<float, 128, 128, 2, 2, 2, true, 0, false, 0>"
                       : "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 0, false, 0>";
     }
@@ -3306,8 +3174,9 @@ hipError_t launch_conv(int dt, const ConvArgs &a0, hipStream_t st) {
     case PP_256: return run_pp<256, 224, 0, false>(a, st);
     case PP_256_P8: return run_pp<256, 224, 8, true>(a, st);
     case PP_256_P16: return run_pp<256, 224, 16, true>(a, st);
-    case ROWS: return run_rows<false>(a, st);
-    case ROWS_P: return run_rows<true>(a, st);
+    case PP_128_P16: return run_pp<128, 128, 16, true>(a, st);
+    case ROWS: return run_rows<false, false>(a, st);
+    case ROWS_P: return a.res ? run_rows<true, true>(a, st) : run_rows<true, false>(a, st);
     case IMG_7: return run_img<7, false>(a, st);
     case IMG_14: return run_img<14, false>(a, st);
     case IMG_7S2: return run_img<7, false, 2>(a, st);

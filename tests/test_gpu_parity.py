@@ -209,19 +209,18 @@ PP_CASES = [
     (64, 64, 28, 28, 512, 2, [0, 63], "conv_pp<256, 224, 8, true>"),
     # ... 14 x 16 tiles where they are fewer (42 x 16 maps: 3 against 4)
     (32, 64, 42, 16, 512, 2, [0, 31], "conv_pp<256, 224, 16, true>"),
-    # the pool in conv_dma's epilogue (8 x 16 tiles), 64 and 128 channels
+    # the pool in the epilogue of conv_dma's 8 x 16 tiles of 64 channels and
+    # conv_pp's of 128
     (4, 32, 96, 112, 64, 2, [1, 3],
      "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 0>"),
-    (8, 64, 64, 96, 128, 2, [5],
-     "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, true, 0>"),
-    # conv_dma with the halo tile (64 input channels): ragged 8 x 16 tiles
-    # (60 x 60 maps), with and without the pool, 64, 40 and 128 channels
-    (9, 64, 60, 60, 64, 2, [0, 8],
-     "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>"),
+    (8, 64, 64, 96, 128, 2, [5], "conv_pp<128, 128, 16, true>"),
+    # 64 input channels, 60 x 60 maps (strips and 8 x 16 tiles past the
+    # map): filters in registers with the pool, conv_dma's halo tile for a
+    # few images of 40 channels, filters in registers without the pool
+    (9, 64, 60, 60, 64, 2, [0, 8], "conv_rows<true, true, false>"),
     (8, 64, 60, 60, 40, 0, [0, 7],
      "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, false, 1>"),
-    (8, 64, 60, 60, 128, 0, [3],
-     "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>"),
+    (8, 64, 60, 60, 128, 0, [3], "conv_rows<false, true, false>"),
     # whole-image kernel at ResNet-18's 14x14 stage size
     (64, 256, 14, 14, 256, 0, [0, 37, 63], "conv_img<14, false, 1>"),
 ]
@@ -229,7 +228,7 @@ PP_CASES = [
 
 @pytest.mark.parametrize("case", PP_CASES)
 def test_conv2d_forward_large_tiles_and_fused_pool(P, case):
-    """Shapes that take the 224-pixel ping-pong kernel or a pooled epilogue
+    """Shapes that take conv_pp's 224-pixel tiles or a pooled epilogue
     (integer data: every sum exact, so any summation order gives the same
     bits).  Unpooled output: equal to the oracle's convolution on the
     sampled images.  Pooled output: bit-identical to the library's own
@@ -388,7 +387,7 @@ NET_CASES = [
 def test_mobilenetv2_expand_convs_take_the_pointwise_kernel(P):
     """The 1x1 convs of MobileNetV2 with at most 64 input channels, or up
     to 160 and at most 192 output channels, run on conv_pw; the others on
-    the implicit GEMM."""
+    the implicit GEMM kernels."""
     net = config("mobilenetv2_f16_b128")
     cn = _net(P, net, gen.make_params(net))
     cn.set_fusion(P.ctc.CTC_FUSE_BLOCK | P.ctc.CTC_FUSE_STEM | P.ctc.CTC_FUSE_POOL)
@@ -404,7 +403,8 @@ def test_mobilenetv2_expand_convs_take_the_pointwise_kernel(P):
     for i in pw:
         assert names[i].startswith("conv_pw<"), (i, names[i])
     wide = [i for i, L in enumerate(net.layers) if pointwise(L) and not narrow(L)]
-    assert wide and all(names[i].startswith("conv_dma<") for i in wide)
+    assert wide and all(names[i].startswith(("conv_dma<", "conv_pp<", "conv_ppr<"))
+                        for i in wide)
 
 
 @pytest.mark.parametrize("label,rows", NET_CASES)
@@ -770,9 +770,9 @@ def test_fused_conv_pool_vgg16(P):
     assert len(pools) == 5 and len(fused) == 4, names
     assert names.count("maxpool_fixed<_Float16, 2, 2>") == 1
     assert any(n.startswith("conv_pp<256, 224, 8, true>") for n in names)
-    # conv1_2 pools in the halo-tile epilogue, conv2_2 in conv_dma's
-    assert "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 16, true, 1>" in names
-    assert "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, true, 0>" in names
+    # conv1_2 pools in the registers of conv_rows, conv2_2 in conv_pp's epilogue
+    assert "conv_rows<true, true, false>" in names
+    assert "conv_pp<128, 128, 16, true>" in names
     x = torch.from_numpy(gen.make_inputs(net, B)).cuda()
     on = cn.forward(x).cpu().numpy()
     pooled_on = [cn.tensor(i + 1, B).cpu().numpy().copy() for i in fused]

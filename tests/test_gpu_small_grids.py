@@ -89,8 +89,7 @@ def test_small_batches_give_the_bits_of_large_ones(case):
 
 # dtype, C, H, W, K, kernel, stride, residual, images, tile; ragged last pixel
 # tiles, one or several channel tiles, 1 (fewer than the stages) to 36 steps
-D3 = "conv_dma<_Float16, %d, %d, 2, 2, 3, true, 0, false, 0>"
-D4 = D3.replace("2, 3", "2, 4")
+PP, PPR = "conv_pp<%d, %d, 0, false>", "conv_ppr<_Float16, %d, %d>"
 TILES = [
     ("f16", 64, 25, 27, 128, 3, 1, True, 6, "conv_pp<128, 32, 0, false>"),
     ("f16", 64, 27, 25, 128, 1, 2, False, 40, "conv_pp<128, 32, 0, false>"),
@@ -104,13 +103,13 @@ TILES = [
     ("f16", 64, 27, 25, 64, 5, 2, True, 250, "conv_pp<64, 96, 0, false>"),
     ("f16", 128, 41, 35, 256, 3, 2, True, 120, "conv_pp<256, 224, 0, false>"),
     ("f16", 256, 29, 27, 256, 3, 1, True, 57, "conv_pp<256, 224, 0, false>"),
-    ("f16", 192, 13, 13, 384, 1, 1, True, 110, D3 % (128, 128)),
-    ("f16", 320, 13, 13, 384, 1, 1, False, 80, D3 % (96, 128)),
-    ("f16", 576, 13, 13, 128, 1, 1, True, 70, D3 % (64, 128)),
-    ("f16", 192, 13, 13, 256, 1, 1, False, 13, D3 % (32, 128)),
-    ("f16", 320, 13, 13, 192, 1, 1, True, 80, D3 % (96, 64)),
-    ("f16", 384, 13, 13, 64, 1, 1, False, 70, D3 % (64, 64)),
-    ("f16", 192, 13, 13, 64, 1, 1, True, 40, D3 % (32, 64)),
+    ("f16", 192, 13, 13, 384, 1, 1, True, 110, PP % (128, 128)),
+    ("f16", 320, 13, 13, 384, 1, 1, False, 80, PP % (128, 96)),
+    ("f16", 576, 13, 13, 128, 1, 1, True, 70, PP % (128, 64)),
+    ("f16", 192, 13, 13, 256, 1, 1, False, 13, PP % (128, 32)),
+    ("f16", 320, 13, 13, 192, 1, 1, True, 80, PP % (64, 96)),
+    ("f16", 384, 13, 13, 64, 1, 1, False, 70, PP % (64, 64)),
+    ("f16", 192, 13, 13, 64, 1, 1, True, 40, PP % (64, 32)),
     # channels that end within a step, channel tiles that end within a tile
     ("f16", 72, 25, 27, 136, 3, 1, True, 5, "conv_ppr<_Float16, 64, 32>"),
     ("f16", 104, 25, 27, 40, 3, 2, False, 60, "conv_ppr<_Float16, 64, 64>"),
@@ -120,12 +119,12 @@ TILES = [
     ("f16", 72, 57, 53, 136, 3, 1, True, 9, "conv_ppr<_Float16, 128, 128>"),
     ("f16", 128, 27, 25, 192, 3, 1, False, 40, "conv_ppr<_Float16, 128, 128>"),
     ("f16", 64, 27, 25, 168, 5, 2, True, 18, "conv_ppr<_Float16, 64, 32>"),
-    ("f16", 200, 13, 13, 232, 1, 1, True, 13, D4 % (32, 128)),
-    ("f16", 264, 13, 13, 96, 1, 1, False, 70, D4 % (64, 128)),
-    ("f16", 192, 13, 13, 232, 1, 1, True, 160, D4 % (128, 128)),
-    ("f16", 328, 13, 13, 136, 1, 1, True, 12, D4 % (32, 64)),
-    ("f16", 576, 13, 13, 160, 1, 1, False, 25, D4 % (64, 64)),
-    ("f16", 168, 13, 13, 160, 1, 1, True, 80, D4 % (96, 64)),
+    ("f16", 200, 13, 13, 232, 1, 1, True, 13, PPR % (128, 32)),
+    ("f16", 264, 13, 13, 96, 1, 1, False, 70, PPR % (128, 64)),
+    ("f16", 192, 13, 13, 232, 1, 1, True, 160, PPR % (128, 128)),
+    ("f16", 328, 13, 13, 136, 1, 1, True, 12, PPR % (64, 32)),
+    ("f16", 576, 13, 13, 160, 1, 1, False, 25, PPR % (64, 64)),
+    ("f16", 168, 13, 13, 160, 1, 1, True, 80, PPR % (64, 96)),
     ("f32", 36, 27, 25, 100, 3, 1, True, 9, "conv_ppr<float, 64, 32>"),
     ("f32", 44, 27, 25, 132, 3, 2, False, 60, "conv_ppr<float, 64, 32>"),
     ("f32", 36, 49, 51, 36, 3, 1, True, 40, "conv_ppr<float, 64, 64>"),
@@ -331,8 +330,7 @@ def test_filters_in_registers_give_the_bits_of_one_image(case):
     g.manual_seed(H)
     d = ctc.layer_desc(64, K, 3, 3, 1, 1, 1, 1, ctc.CTC_ROLE_SUM)
     assert ctc.ctc_conv2d_kernel_name(d, ctc.CTC_F16, n, H, W) == (
-        "conv_rows4<false>" if K % 8 else
-        "conv_dma<_Float16, 128, 128, 2, 2, 2, true, 16, false, 1>")
+        "conv_rows<false, %s, false>" % ("false" if K % 8 else "true"))
     x = torch.randn((n, H, W, 64), device="cuda", generator=g).half()
     w = (torch.randn((K, 3, 3, 64), device="cuda", generator=g) / 24).half()
     scale = torch.rand(K, device="cuda", generator=g) + 0.5
