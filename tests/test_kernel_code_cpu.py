@@ -58,13 +58,25 @@ def test_results_are_rounded_to_fp32_before_fp16(kernels):
     assert not once, once
 
 
+def _regs(operand):
+    """VGPRs and AGPRs of an operand, as a set of (file, number)."""
+    m = re.match(r"([va])(?:(\d+)|\[(\d+):(\d+)\])$", operand.strip())
+    if not m:
+        return set()
+    lo, hi = (m.group(2), m.group(2)) if m.group(2) else m.group(3, 4)
+    return {(m.group(1), r) for r in range(int(lo), int(hi) + 1)}
+
+
+def test_every_instance_is_checked(code):
+    """conv_pp's instances by kind: a kernel added or lost shows here."""
+    kinds = [re.search(r"conv_pp(r|32)?I", n).group(0) for n in code]
+    assert {k: kinds.count(k) for k in kinds} == {
+        "conv_ppI": 11, "conv_pprI": 8, "conv_pp32I": 2}, sorted(code)
+
+
 def test_accumulators_of_inline_mfmas_are_touched_only_at_a_distance(code):
-    checked = 0
     for name, ins in code.items():
         waits = [i for i, s in enumerate(ins) if s == "s_nop 11"]
-        if not waits:
-            continue                    # the compiler's own MFMAs
-        checked += 1
         assert len(waits) == 1, name
         # the loop up to the wait is one basic block
         top = max(i for i in range(waits[0]) if re.match("s_c?branch", ins[i]))
@@ -72,7 +84,22 @@ def test_accumulators_of_inline_mfmas_are_touched_only_at_a_distance(code):
         uses = [i for i, s in enumerate(ins[:waits[0]])
                 if AGPR.search(s) and not s.startswith("v_mfma")]
         assert len(mfma) >= 4 and "a[" in ins[mfma[0]], name
+        # no MFMA outside the block whose end waits
+        assert sum(s.startswith("v_mfma") for s in ins) == len(mfma), name
         near = [ins[i] for i in uses if i > mfma[0] - 8]
         # (zeroed accumulators: well ahead of the first MFMA)
         assert not near, (name, near[:5])
-    assert checked >= 20, sorted(code)
+
+
+def test_operands_of_inline_mfmas_are_written_at_a_distance(code):
+    """A vector instruction may write an operand of an MFMA two wait states
+    before it at the latest (fragments come from LDS, behind a waitcnt)."""
+    for name, ins in code.items():
+        for i, s in enumerate(ins):
+            if not s.startswith("v_mfma"):
+                continue
+            src = set().union(*(_regs(o) for o in s.split(None, 1)[1].split(",")[1:]))
+            for p in ins[i - 2:i]:
+                if p.startswith("v_") and not p.startswith("v_mfma"):
+                    dst = _regs(p.split(None, 1)[1].split(",")[0])
+                    assert not dst & src, (name, p, s)
