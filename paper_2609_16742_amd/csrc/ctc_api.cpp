@@ -2634,6 +2634,7 @@ ctc_status ctc_net_op_kernel(const ctc_net *net, int32_t i, int32_t nimg,
         a.nimg = nimg; a.Cs = ti.cs; a.N = o.c_out;
         a.H = ti.h; a.W = ti.w; a.P = to.h; a.Q = to.w;
         a.R = o.k; a.S = o.k; a.stride = o.stride; a.pad = o.pad;
+        a.res = o.residual >= 0 ? (const void *)1 : nullptr;    // naming only
         a.part = net->part_bytes ? (float *)1 : nullptr;    // naming only
         int head = -1;                      // fused IR block containing op i
         for (int h = i; h >= 0 && h >= i - 2; h--)

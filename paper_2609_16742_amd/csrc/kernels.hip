@@ -3012,34 +3012,76 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
 }
 
 // Whether a layer that select_conv gives to `c` runs on conv_lat at this
-// batch: up to 2048 tiles of 16 pixels x 16 channels, 8 per CU.  Measured
-// there, other kernel -> conv_lat: fp16, one image, 28x28x128 (392 tiles) 8.6
-// -> 5.9 us, 28x28x512 (1568) 36.1 -> 19.0, 14x14x256 (208) 28.3 -> 5.7,
-// 7x7x512 (128) 15.4 -> 8.3, eight images 14x14x256 (1664) 28.7 -> 13.4; fp32
-// 28x28x128 16.7 -> 10.4, 14x14x256 29.8 -> 16.0, at eight (1568) 31.3 ->
-// 26.1.  Above the line the tiles that share rows win back what they lose in
-// latency: fp32 56x56x64 15.4 -> 18.8 at 3136 tiles, 28x28x72 -> 136 10.8 ->
-// 14.7 at 3528, 14x14 96 -> 576 1x1 5.7 -> 9.3 at 3600.  The line is lower
-// where the other kernel has small tiles itself: 1600 next to conv_pp's in
-// fp16 (28x28x128 8.8 -> 8.4 at 1568, 9.0 -> 11.9 at 2352), or 1024 if k is
-// short too (56x56 64 -> 128 stride 2 6.3 -> 5.7 at 784, 6.4 -> 6.9 at 1568),
-// and 512 next to the 64-channel ones (56x56x64 5.3 -> 5.7 at 784; 28x28 256
-// -> 64, long in k, 10.8 -> 7.0); 1024 next to conv_pw (96 -> 576 5.4 -> 4.6
-// us at 468 tiles, 5.5 -> 5.6 at 1800) and on 7x7 maps (512 channels 15.8 ->
-// 12.0 us at 800, 16.3 -> 22.4 at 1696).
+// batch.  Measured there, other kernel -> conv_lat: fp16, one image, 28x28x128
+// (392 tiles of 16 pixels x 16 channels) 8.6 -> 5.9 us, 28x28x512 (1568) 36.1
+// -> 19.0, 14x14x256 (208) 28.3 -> 5.7, 7x7x512 (128) 15.4 -> 8.3, eight images
+// 14x14x256 (1664) 28.7 -> 13.4; fp32 28x28x128 16.7 -> 10.4, 14x14x256 29.8 ->
+// 16.0, at eight (1568) 31.3 -> 26.1.
+// The lines below come from 16101 layers of at most 2048 tiles (drawn sizes and
+// the networks' layers at every batch), each on both kernels:
+//  - Up to 1024 tiles, one wave per SIMD, conv_lat gains 10% to 4 times, the
+//    more the longer k is; with fewer steps than it takes to fill its ring it
+//    only pays for the ring.  Steps (128 bytes of k) from which it is ahead:
+//    in fp16 where channels end within one, seven next to conv_ppr's 64-channel
+//    tiles (14x14 96 -> 576 1x1, two steps, 3.5 us against 4.0 on conv_lat) and
+//    four of 3x3 next to conv_dma's 32-channel ones (72x72 16 -> 24, three
+//    steps, 4.6 against 4.9); three in fp32; two or one elsewhere.
+//  - Above, a SIMD's second wave costs what the first did.  It still is ahead
+//    of a kernel that runs a second round itself (fp32, more than 256 tiles of
+//    32 pixels x 64 channels: 20% against -9%), that has no tile for the layer
+//    (conv_dma, 20%), or that waits on the filters (more than 3 MB, 15 to 75%);
+//    and, as its channel tiles are spread over the XCDs, where each XCD's L2
+//    holds the whole input (4 MB: 8 to 20% against -15%).
+//  - The ranges of a split layer are four waves a tile: 512 tiles, 1024 with
+//    whole steps (fp32: 2048); 7x7x520 fp16 at 16 images (1617) 20.9 us against
+//    42.7 on conv_lat.
+//  - conv_pw is ahead up to 64 channels (63x63 16 -> 16 at two images 2.6 us
+//    against 4.8, 19x15 32 -> 32 at 13 2.9, 4.3), up to 48 past 96 input
+//    channels, and at any number of up to 32 input channels unless there are
+//    more than 128 and a residual (28x28 32 -> 192 6.3 us, conv_lat 4.5).
 static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
-    const int es = dt == DT_F32 ? 4 : 2;
+    const bool f32 = dt == DT_F32;
+    const int es = f32 ? 4 : 2, ks = 128 / es;
     if (a.pool || (c < D_64x32 && c != PW_F16 && !img_cfg(c))) return false;
-    if (a.Cs % (16 / es) || (long)a.nimg * a.H * a.W * a.Cs * es >= (1l << 31) ||
-        (long)a.N * a.R * a.S * a.Cs * es >= (1l << 31))
-        return false;
-    const long M = (long)a.nimg * a.P * a.Q, tiles = (M + 15) / 16 * ((a.N + 15) / 16);
-    if (c == PW_F16 || c == IMG_7 || c == IMG_7S2) return tiles <= 1024;
-    if (dt == DT_F16 && pp_tile(dt, a, c)) {
-        const bool shortk = a.R * a.S * a.Cs <= 576;
-        return tiles <= (!shortk ? 1600 : a.N % 128 ? 512 : 1024);
+    const long K = (long)a.R * a.S * a.Cs;
+    const long xbytes = (long)a.nimg * a.H * a.W * a.Cs * es, wbytes = a.N * K * es;
+    if (a.Cs % (16 / es) || xbytes >= (1l << 31) || wbytes >= (1l << 31)) return false;
+    const long M = (long)a.nimg * a.P * a.Q, nt = (a.N + 15) / 16, tiles = (M + 15) / 16 * nt;
+    if (tiles > 2048) return false;
+    if (c == IMG_14) return true;
+    if (c == IMG_7 || c == IMG_7S2) return tiles <= 1024;
+    if (c == PW_F16)
+        return tiles <= 1024 &&
+               (a.Cs > 96 ? a.N > 48 : a.Cs > 32 ? a.N > 64 : a.res && a.N > 128);
+    const long steps = (K + ks - 1) / ks;
+    const bool whole = a.Cs % ks == 0, second = tiles > 1024;
+    if (a.part && conv_splitk(dt, a) > 1) return tiles <= (!whole ? 512 : f32 ? 2048 : 1024);
+    if (const PpTile *t = pp_tile(dt, a, c)) {
+        if (f32) {
+            if (steps < (whole ? 2 : 3)) return false;
+            const bool rounds = (M + 31) / 32 * ((a.N + 63) / 64) > 256;
+            if (!second) return true;
+            return whole ? steps > 31 || wbytes > 500000 || (rounds && steps > 2)
+                         : rounds && a.R > 1;
+        }
+        // (short in k: conv_pp's tiles of 128 and 64 channels are ahead from
+        // 1024 and 512 tiles on: 56x56 64 -> 128 stride 2 6.3 us against 5.7 on
+        // conv_lat at 784, 6.4 against 6.9 at 1568; 56x56x64 5.3, 5.7 at 784)
+        if (tiles > (K > 576 ? 1600 : a.N % 128 ? 512 : 1024)) return false;
+        if (steps < (t->bn == 128 ? (whole ? 1 : 2) : whole ? 2 : 7)) return false;
+        return !second || (wbytes > 3000000 && (whole || t->bn == 128)) ||
+               (whole && t->bn == 128 && (xbytes < (4l << 20) || tiles <= 1216));
     }
-    return tiles <= 2048;
+    if (a.N <= 32) {
+        if (f32) return steps >= (!second ? (whole ? 1 : 2) : whole ? 3 : 7);
+        if (!second) return whole || steps >= (a.R == 1 ? 2 : 4);
+        return steps >= 8 ? whole || tiles <= 1360 || nt == 1
+                          : whole && steps >= 4 && tiles <= 1360;
+    }
+    if (second) return steps >= (f32 ? 5 : 3);
+    // (one step of fp16: conv_dma's 64 x 64 tiles of 3, 5 .. channel tiles)
+    const long n64 = (a.N + 63) / 64;
+    return f32 || steps > 1 || n64 == 1 || n64 % 2 == 0;
 }
 
 const char *conv_kernel_name(int dt, const ConvArgs &a) {

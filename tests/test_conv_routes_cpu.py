@@ -1,0 +1,36 @@
+"""Which kernel a convolution runs on, at the lines between kernels: the names
+that libctc.so gives need no GPU.  What the kernels compute there is the GPU
+tests' matter."""
+import pytest
+
+ctc = pytest.importorskip("paper_2609_16742_amd.ctc")
+
+
+def _name(dtype, n, h, w, c_in, c_out, k, stride=1):
+    d = ctc.layer_desc(c_in, c_out, k, k, stride, k // 2, 1, 1, ctc.CTC_ROLE_SUM)
+    return ctc.ctc_conv2d_kernel_name(d, ctc.DTYPES[dtype], n, h, w)
+
+
+# layer, whether conv_lat (one wave per 16 x 16 output tile) is the faster kernel
+LAT = [
+    # pointwise: conv_pw up to 64 (48) channels
+    (("f16", 2, 63, 63, 16, 16, 1), False), (("f16", 13, 19, 15, 32, 32, 1), False),
+    (("f16", 1, 28, 28, 64, 64, 1), False), (("f16", 1, 28, 28, 64, 72, 1), True),
+    (("f16", 1, 14, 14, 160, 48, 1), False), (("f16", 1, 14, 14, 160, 56, 1), True),
+    (("f16", 1, 14, 14, 32, 256, 1), False), (("f16", 1, 14, 14, 96, 512, 1), True),
+    # few steps of k
+    (("f16", 1, 72, 72, 16, 24, 3), False), (("f16", 1, 72, 72, 24, 24, 3), True),
+    (("f16", 2, 36, 36, 144, 96, 1, 2), True), (("f16", 1, 28, 28, 144, 168, 1, 2), False),
+    (("f16", 1, 14, 14, 96, 576, 1), False), (("f16", 1, 14, 14, 392, 576, 1), True),
+    (("f32", 1, 14, 14, 36, 96, 1), False), (("f32", 1, 14, 14, 68, 96, 1), True),
+    # one wave per SIMD and more of them
+    (("f16", 4, 14, 14, 264, 264, 3), True), (("f16", 5, 14, 14, 264, 264, 3), False),
+    (("f16", 4, 28, 28, 128, 128, 3), True), (("f16", 1, 28, 28, 512, 512, 3), True),
+    (("f32", 4, 14, 14, 260, 260, 3), True), (("f32", 5, 14, 14, 260, 260, 3), False),
+    (("f32", 8, 14, 14, 256, 256, 3), True), (("f32", 12, 28, 28, 36, 40, 3), True),
+]
+
+
+@pytest.mark.parametrize("layer,lat", LAT)
+def test_small_layers_take_the_faster_kernel(layer, lat):
+    assert _name(*layer).startswith("conv_lat") == lat, _name(*layer)

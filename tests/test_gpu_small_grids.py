@@ -17,8 +17,8 @@ CASES = [
     ("f16", 8, 17, 9, 260, 3, 2, False, 2, 64, "<_Float16, false, false, 1>"),
     # pointwise layers, conv_pw's among them
     ("f16", 960, 7, 7, 160, 1, 1, True, 1, 70, "<_Float16, false, true, 1>"),
-    ("f16", 96, 14, 14, 576, 1, 1, False, 1, 8, "<_Float16, false, false, 1>"),
-    ("f16", 24, 13, 11, 36, 1, 1, False, 3, 100, "<_Float16, false, false, 1>"),
+    ("f16", 96, 14, 14, 512, 1, 1, False, 1, 8, "<_Float16, false, false, 1>"),
+    ("f16", 40, 13, 11, 68, 1, 1, False, 3, 100, "<_Float16, false, false, 1>"),
     # whole-image layers: one to four planes, odd counts, stride 2
     ("f16", 64, 7, 7, 64, 3, 1, True, 3, 180, "<_Float16, true, true, 1>"),
     ("f16", 192, 7, 7, 128, 3, 1, False, 2, 90, "<_Float16, true, true, 1>"),
@@ -85,6 +85,24 @@ def test_small_batches_give_the_bits_of_large_ones(case):
     err = (ys.cpu().double().permute(0, 3, 1, 2) - ref.relu()).norm()
     # one rounding to 11 bits, or sums of K <= 4644 products in fp32
     assert err <= (2.0 ** -11 if dtype == "f16" else 1e-5) * ref.norm()
+
+
+@pytest.mark.parametrize("dtype,protect,last", [("f32", "replace", 20), ("f16", "append", 4)])
+def test_layers_split_over_k_leave_conv_lat_past_their_line(dtype, protect, last):
+    """ResNet-18's 7x7 layers split k over four waves of conv_lat up to 2048
+    tiles (fp32, whole steps of channels) or 512 (appended channels)."""
+    import paper_2609_16742_amd as P
+    from workloads import gen, nets
+    net = nets.by_name("resnet18", dtype=dtype)
+    print("split", dtype, protect, flush=True)
+    cn = P.CtcNet(net.layers, net.in_shape, net.classes, dtype, gen.make_params(net),
+                  protect=protect, max_batch=64)
+    ops = [i for i, L in enumerate(net.layers)
+           if L["op"] == "conv" and L["c_in"] == 512 and L["k"] == 3]
+    for n in (1, last, last + 1, 64):
+        names = {P.ctc.ctc_net_op_kernel(cn.h, i, n) for i in ops}
+        assert len(names) == 1, names
+        assert names.pop().startswith("conv_lat" if n <= last else "conv_dma"), n
 
 
 # dtype, C, H, W, K, kernel, stride, residual, images, tile; ragged last pixel
