@@ -2927,31 +2927,45 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
 
 // conv_pp's smaller tiles, for the layers of conv_dma that have at least one
 // 128-byte k step of input channels and whole 16-byte pieces of output
-// channels and are not split over k.  The rows of a table go from the largest tile to the smallest, and a layer takes
-// the first that leaves at least `tiles` of them: 1.5 workgroups per CU keep
-// the matrix cores busy, then smaller tiles spread the pixels over more CUs.
+// channels and are not split over k.  The rows of a table go from the largest
+// tile to the smallest, and a layer takes the first that leaves at least
+// `tiles` of them: more than one per CU for the largest, then smaller tiles
+// spread the pixels over more CUs.
 // conv_dma -> these, measured in graphs, fp16, 3x3: 28x28x128 at batch 8
 // 15.2 -> 9.3 us (32 pixels; 64: 10.6), 16 15.9 -> 11.2 (64), 32 19.2 -> 15.3
 // (64; 96: 16.4), 48 23.8 -> 19.7 (96); 28x28x512 at 16 78 -> 68 (128), 24 118
 // -> 106; 56x56 64 -> 128 stride 2 at 32 12.9 -> 10.5; 28x28 128 -> 256 stride
 // 2, 1x1, at 256 18.9 -> 15.9.  Channel counts that are no multiple of 128:
 // 15x15x64 at batch 50 10.8 -> 6.5, 200 11.5 -> 9.7, 400 16.5 -> 16.2, 30x30
-// 128 -> 64 at 120 36.3 -> 31.7, 19x19 512 -> 64 at 33 47.1 -> 25.1.  Channel
-// counts that fill neither tile (64 channels past a multiple of 128, or parts
-// of 64) take padded 128-channel tiles where 384 of them are left and the
-// padding is below 30%, and channels that end within a step (RAG) cost a few
-// address instructions: 20x20 256 -> 192 at 160 79.7 -> 74.6, 28x28 256 -> 320
-// at 64 103 -> 90, 96 -> 320 54.7 -> 47.1, 96 -> 96 23.0 -> 19.0, 57x53 72 -> 136
-// at 24 39.9 -> 37.9 (28x28 at 64 with a residual 30.7 -> 31.7), 7x7 960 -> 160
-// 1x1 at 128 11.7 -> 9.8.  conv_dma stays for stride-1 1x1 layers that write
-// more than they compute: with a residual 14x14 96 -> 576 at 256 39.5 us
-// against 43.3, 17x17 192 -> 320 at 64 12.0 against 13.2.
-// 1x1: 7x7 320 -> 1280 at batch 128 15.5 -> 13.6 us, 2048 -> 512 at 64 23.4 -> 17.6 (64 pixels), 14x14 512 ->
-// 256 at 128 18.0 -> 15.2, 56x56 256 -> 512 at 64 134 -> 121.
+// 128 -> 64 at 120 36.3 -> 31.7, 19x19 512 -> 64 at 33 47.1 -> 25.1.
+// 1x1: 7x7 320 -> 1280 at batch 128 15.5 -> 13.6 us, 2048 -> 512 at 64 23.4 ->
+// 17.6 (64 pixels), 14x14 512 -> 256 at 128 18.0 -> 15.2, 56x56 256 -> 512 at 64
+// 134 -> 121.
 // fp32: 28x28x128 at batch 64 145.9 -> 136.2 us, 14x14x256 163 -> 140 (64 x
 // 64: 150), 14x14 1024 -> 256 1x1 at 16 30.5 -> 24.4; many tiles with a short
 // k pay for the smaller tile's loads: 56x56x64 at 64 140.6 -> 133.4 (64 x 32:
 // 137.1), 56x56 64 -> 256 1x1 133 -> 121 (148).
+// Lines between the fp16 tiles, from 6781 layers around them, mean and worst
+// gain over conv_dma:
+//  - Two 128 x 64 tiles share a CU.  Up to 256 tiles of 128 x 128 (512 of 128 x
+//    64) they gain 14% (worst 0.98), past that they need a second round: 0.92
+//    (0.71) where 128 x 128 tiles gain 8% (channels past a step or a tile) and
+//    128 x 96 17% (whole ones).
+//  - Three 64 x 96 tiles share a CU: up to 512 they gain 18 to 20%; from 513 to
+//    680 some CUs have three and most two, and layers with channels past a step
+//    and more than 18 steps lose (0.93): conv_dma keeps them; up to 768 12 to
+//    16% again; from 769 to 1024, a second round, 0.94.
+//  - Channel counts in an odd number of 64s, from 192 on, take padded 128 x 128
+//    tiles past those 768: 10% up to 1024 tiles, 13 to 20% above, at 33% padding
+//    for 192 and less for more channels (20x20 256 -> 192 at 160 79.7 -> 74.6 us,
+//    28x28 256 -> 320 at 64 103 -> 90, 57x53 72 -> 136 at 24 39.9 -> 37.9);
+//    conv_dma keeps up to 64 channels there unless k is long (31 steps).
+//  - conv_dma also keeps stride-1 1x1 layers that write more than they compute,
+//    with channels past a step or a tile: less than 160 input channels past 384
+//    tiles of 128 x 128 (14x14 96 -> 576 with a residual at 256 39.5 us against
+//    43.3), less than 192 with a residual from 257 to 512 (0.83 to 0.91; 7x7
+//    160 -> 960 at 128 10.6 against 12.0; at 5145, 56x56 168 -> 864 at 30, 163
+//    against 125).
 struct PpTile {
     int bn, bm;
     long tiles;
@@ -2960,7 +2974,7 @@ struct PpTile {
 };
 static const PpTile PP_F16[] = {
     {128, 128, 384, "conv_pp<128, 128, 0, false>", run_pp<128, 128, 0, false>},
-    {128, 96, 384, "conv_pp<128, 96, 0, false>", run_pp<128, 96, 0, false>},
+    {128, 96, 343, "conv_pp<128, 96, 0, false>", run_pp<128, 96, 0, false>},
     {128, 64, 160, "conv_pp<128, 64, 0, false>", run_pp<128, 64, 0, false>},
     {128, 32, 0, "conv_pp<128, 32, 0, false>", run_pp<128, 32, 0, false>},
     {64, 96, 384, "conv_pp<64, 96, 0, false>", run_pp<64, 96, 0, false>},
@@ -2968,7 +2982,7 @@ static const PpTile PP_F16[] = {
     {64, 32, 0, "conv_pp<64, 32, 0, false>", run_pp<64, 32, 0, false>},
 };
 static const PpTile PPR_F16[] = {
-    {128, 128, 384, "conv_ppr<_Float16, 128, 128>", run_ppr<_Float16, 128, 128>},
+    {128, 128, 257, "conv_ppr<_Float16, 128, 128>", run_ppr<_Float16, 128, 128>},
     {128, 64, 160, "conv_ppr<_Float16, 128, 64>", run_ppr<_Float16, 128, 64>},
     {128, 32, 0, "conv_ppr<_Float16, 128, 32>", run_ppr<_Float16, 128, 32>},
     {64, 96, 384, "conv_ppr<_Float16, 64, 96>", run_ppr<_Float16, 64, 96>},
@@ -2990,8 +3004,9 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
         return nullptr;
     const bool pw = a.R == 1 && a.S == 1 && a.stride == 1;
     const long M = (long)a.nimg * a.P * a.Q, n64 = (a.N + 63) / 64, n128 = (a.N + 127) / 128;
+    const long t128 = (M + 127) / 128 * n128, t96 = (M + 95) / 96 * n64;
     // (fp16) 128 x 128 tiles on a channel count that does not fill them
-    const bool big = n64 % 2 && n128 * 90 <= n64 * 64 && (M + 127) / 128 * n128 >= 384;
+    const bool big = n64 % 2 && n64 > 1 && t96 > 768;
     const bool rag = a.Cs % ks || a.N % 64 || (ks == 64 && !pw && big);
     if (rag && (a.Cs < ks || a.N <= 32 || a.N % (ks / 8))) return nullptr;
     if (dt == DT_F32) {
@@ -3000,8 +3015,13 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
         return &t[!shortk || (M + 63) / 64 * n64 < t[0].tiles];
     }
     const int bn = n64 % 2 == 0 || (rag && big) ? 128 : 64;
-    if (pw && (rag ? a.Cs < 160 && (M + 127) / 128 * n128 >= 384
-                   : bn == 64 && a.N > 64 && (M + 95) / 96 * n64 > 768))
+    if (pw && (rag ? a.Cs < 160 && t128 >= 384 : bn == 64 && a.N > 64 && t96 > 768))
+        return nullptr;
+    if (pw && rag && bn == 128 && a.res && a.Cs < 192 && t128 > 256 && t128 <= 512)
+        return nullptr;
+    const long steps = ((long)a.R * a.S * a.Cs + ks - 1) / ks;
+    if (bn == 64 && ((a.Cs % ks && steps > 18 && t96 > 512 && t96 <= 680) ||
+                     (a.N <= 64 && steps <= 30 && t96 > 768 && t96 <= 1024)))
         return nullptr;
     auto pick = [&](auto &tab) -> const PpTile * {
         for (const PpTile &t : tab)

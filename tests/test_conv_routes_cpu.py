@@ -34,3 +34,30 @@ LAT = [
 @pytest.mark.parametrize("layer,lat", LAT)
 def test_small_layers_take_the_faster_kernel(layer, lat):
     assert _name(*layer).startswith("conv_lat") == lat, _name(*layer)
+
+
+# layer, its kernel: the lines between conv_pp's tiles, which are its rounds of
+# workgroups
+TILES = [
+    # 256 tiles of 128 x 128 (two 128 x 64 tiles per CU), one more pixel tile
+    (("f16", 1, 128, 128, 128, 256, 3), "conv_pp<128, 64, 0, false>"),
+    (("f16", 1, 128, 129, 128, 256, 3), "conv_pp<128, 96, 0, false>"),
+    (("f16", 1, 128, 128, 136, 248, 3), "conv_ppr<_Float16, 128, 64>"),
+    (("f16", 1, 128, 129, 136, 248, 3), "conv_ppr<_Float16, 128, 128>"),
+    # 64 x 96 tiles: 510 (512), 684 (680), 768, 771, 1026 (1024) of them
+    (("f16", 1, 96, 170, 264, 168, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 1, 96, 171, 264, 168, 3), "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 0, false, 0>"),
+    (("f16", 1, 96, 171, 104, 168, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 1, 96, 228, 264, 168, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 1, 96, 256, 264, 168, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 1, 96, 257, 264, 168, 3), "conv_ppr<_Float16, 128, 128>"),
+    (("f16", 1, 96, 768, 136, 64, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 1, 96, 769, 136, 64, 3), "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 0, false, 0>"),
+    (("f16", 1, 96, 769, 264, 64, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 1, 96, 1025, 136, 64, 3), "conv_ppr<_Float16, 64, 96>"),
+]
+
+
+@pytest.mark.parametrize("layer,name", TILES)
+def test_layers_take_the_tile_of_their_rounds(layer, name):
+    assert _name(*layer) == name

@@ -140,6 +140,10 @@ TILES = [
     ("f16", 200, 13, 13, 232, 1, 1, True, 13, PPR % (128, 32)),
     ("f16", 264, 13, 13, 96, 1, 1, False, 70, PPR % (128, 64)),
     ("f16", 192, 13, 13, 232, 1, 1, True, 160, PPR % (128, 128)),
+    # little more than one 128 x 128 tile per CU; an odd number of 64 channels
+    ("f16", 136, 27, 25, 248, 3, 1, True, 25, PPR % (128, 128)),
+    ("f16", 128, 27, 25, 256, 3, 1, False, 25, "conv_pp<128, 96, 0, false>"),
+    ("f16", 72, 27, 25, 312, 3, 1, True, 23, PPR % (128, 128)),
     ("f16", 328, 13, 13, 136, 1, 1, True, 12, PPR % (64, 32)),
     ("f16", 576, 13, 13, 160, 1, 1, False, 25, PPR % (64, 64)),
     ("f16", 168, 13, 13, 160, 1, 1, True, 80, PPR % (64, 96)),
