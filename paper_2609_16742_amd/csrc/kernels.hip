@@ -8,6 +8,7 @@
 
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <mutex>
 #include <type_traits>
@@ -3049,9 +3050,10 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
 //  - Above, a SIMD's second wave costs what the first did.  It still is ahead
 //    of a kernel that runs a second round itself (fp32, more than 256 tiles of
 //    32 pixels x 64 channels: 20% against -9%), that has no tile for the layer
-//    (conv_dma, 20%), or that waits on the filters (more than 3 MB, 15 to 75%);
-//    and, as its channel tiles are spread over the XCDs, where each XCD's L2
-//    holds the whole input (4 MB: 8 to 20% against -15%).
+//    (conv_dma, 20%), or that waits on the filters (more than 3 MB, 15 to 75%;
+//    4 MB next to conv_ppr's 64-channel tiles); and, as its channel tiles are
+//    spread over the XCDs, where each XCD's L2 holds all of the input that is
+//    read (4 MB: 8 to 20% against -15%).
 //  - The ranges of a split layer are four waves a tile: 512 tiles, 1024 with
 //    whole steps (fp32: 2048); 7x7x520 fp16 at 16 images (1617) 20.9 us against
 //    42.7 on conv_lat.
@@ -3089,8 +3091,9 @@ static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
         // conv_lat at 784, 6.4 against 6.9 at 1568; 56x56x64 5.3, 5.7 at 784)
         if (tiles > (K > 576 ? 1600 : a.N % 128 ? 512 : 1024)) return false;
         if (steps < (t->bn == 128 ? (whole ? 1 : 2) : whole ? 2 : 7)) return false;
-        return !second || (wbytes > 3000000 && (whole || t->bn == 128)) ||
-               (whole && t->bn == 128 && (xbytes < (4l << 20) || tiles <= 1216));
+        return !second || wbytes > (whole || t->bn == 128 ? 3000000 : 4000000) ||
+               (whole && (std::min(xbytes, M * K * es) < (4l << 20) ||
+                          (t->bn == 128 && tiles <= 1216)));
     }
     if (a.N <= 32) {
         if (f32) return steps >= (!second ? (whole ? 1 : 2) : whole ? 3 : 7);
