@@ -2823,12 +2823,17 @@ static bool halo_ok(const ConvArgs &a) {
 // 112x112 64 -> 192 at 2 16.5 -> 12.3, 64 -> 256 at 32 154 -> 105; 40x40x64 (a
 // sixth past the map) at 32 11.6 -> 11.2, 20x20 64 -> 128 (3/8) at 400 39.2 ->
 // 40.3.  Channel counts that fill a part of 64, conv_dma -> this: 60x60 64 ->
-// 40 at 64 30.0 -> 21.0 us, 64 -> 96 54.7 -> 37.0, 64 -> 100 67 -> 46.
+// 40 at 64 30.0 -> 21.0 us, 64 -> 96 54.7 -> 37.0, 64 -> 100 67 -> 46.  Up to 32
+// channels leave half of the waves without work: where the halo tile does not
+// fit either, conv_dma's 32-channel tiles stay ahead up to 4608 rows (28x28 64
+// -> 8 with a residual at 57 images, 3192 rows, 8.2 us against 9.5; behind
+// from 5000 on, by 20% at 9000).
 static bool rows_ok(const ConvArgs &a) {
     const long strips = (a.Q + 15) / 16, px = (long)a.nimg * a.H * a.W;
     return !a.pool && a.Cs == 64 && a.R == 3 && a.S == 3 && a.stride == 1 && a.pad == 1 &&
            a.N % 4 == 0 && a.N <= 256 && strips * 16 * 5 <= a.Q * 6l &&
-           a.nimg * strips * a.P * ((a.N + 63) / 64) >= 3072 && px * 128 < (1l << 31) &&
+           a.nimg * strips * a.P * ((a.N + 63) / 64) >=
+               (a.N <= 32 && !halo_ok(a) ? 4608 : 3072) && px * 128 < (1l << 31) &&
            px * a.N * 2 < (1l << 31);
 }
 

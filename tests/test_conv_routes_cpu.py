@@ -55,6 +55,12 @@ TILES = [
     (("f16", 1, 96, 769, 136, 64, 3), "conv_dma<_Float16, 128, 64, 2, 2, 2, true, 0, false, 0>"),
     (("f16", 1, 96, 769, 264, 64, 3), "conv_ppr<_Float16, 64, 96>"),
     (("f16", 1, 96, 1025, 136, 64, 3), "conv_ppr<_Float16, 64, 96>"),
+    # filters in registers: 3072 strip rows, 4608 up to 32 channels
+    (("f16", 54, 28, 28, 64, 40, 3), "conv_ppr<_Float16, 64, 96>"),
+    (("f16", 55, 28, 28, 64, 40, 3), "conv_rows<false, true, false>"),
+    (("f16", 82, 28, 28, 64, 32, 3), "conv_dma<_Float16, 64, 32, 4, 1, 2, true, 0, false, 0>"),
+    (("f16", 83, 28, 28, 64, 32, 3), "conv_rows<false, true, false>"),
+    (("f16", 14, 56, 56, 64, 32, 3), "conv_rows<false, true, false>"),
 ]
 
 

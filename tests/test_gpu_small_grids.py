@@ -337,7 +337,7 @@ ROWS = [
     (16, 60, 60, 64, True), (9, 60, 60, 128, False), (34, 33, 61, 64, False),
     (5, 150, 97, 64, True), (1, 181, 257, 128, True), (200, 18, 16, 64, True),
     (10, 57, 94, 192, False), (5, 57, 45, 256, True), (19, 57, 45, 40, True),
-    (19, 57, 45, 12, True), (19, 45, 77, 32, False),
+    (27, 57, 45, 12, True), (19, 45, 77, 32, False),
     (20, 60, 44, 96, False), (8, 60, 60, 100, True), (30, 33, 61, 68, True),
 ]
 
