@@ -5069,15 +5069,17 @@ __device__ __forceinline__ f16x8 bn_relu_h8(const float (&s)[8], f32x4 sa, f32x4
 
 // Workgroups per CU that conv_ir's LDS leaves room for, up to three (its
 // registers; at two or more the compiler keeps the MFMA results in VGPRs,
-// where the BN reads them, and not in AGPRs).  With this and the packed ReLU,
-// which together take a fifth of the vector instructions out of a kernel that
-// issues one in 87% of its cycles, MobileNetV2's blocks at batch 128: 56x56
-// 16 -> 24 stride 2 102 -> 93 us, 24 -> 24 93 -> 88, 28x28 32 -> 32 35.6 -> 33.4,
-// all together 510 -> 474.
+// where the BN reads them, and not in AGPRs), two with two output tiles a wave.
+// MobileNetV2's blocks at batch 128, traced on one card, us a launch: before,
+// with the packed ReLU, with this as well: <1, 32, 1, 64> 50.5, 49.0, 47.6;
+// <2, 32, 1, 32> 71.6, 62.4, 60.7; <1, 96, 2, 64> 34.9, 34.0, 33.7 (three: 35.0);
+// <1, 64, 1, 64> 21.9, 21.4, 20.8; <1, 64, 2, 64> 23.9, 23.3, 23.3; <2, 32, 1, 64>
+// 16.9, 16.2, 15.1; all of a pass 471, 443, 432.
 constexpr int ir_wgs(int ST, int CP, int COW, int EC) {
     const int hp = 7 * ST + 3, nh = (hp * hp + 15) / 16 * 16;
     const int lds = nh * (CP * 2 + 16) + (nh + 64) * (EC * 2 + 16), n = 163840 / lds;
-    return COW > 2 ? 1 : n > 3 ? 3 : n;
+    const int most = COW > 1 ? 2 : 3;
+    return COW > 2 ? 1 : n > most ? most : n;
 }
 template <int ST, int CP, int COW, int EC>
 __global__ __launch_bounds__(256, ir_wgs(ST, CP, COW, EC)) void conv_ir(IrArgs a) {
