@@ -2963,15 +2963,18 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
 //    16% again; from 769 to 1024, a second round, 0.94.
 //  - Channel counts in an odd number of 64s, from 192 on, take padded 128 x 128
 //    tiles past those 768: 10% up to 1024 tiles, 13 to 20% above, at 33% padding
-//    for 192 and less for more channels (20x20 256 -> 192 at 160 79.7 -> 74.6 us,
-//    28x28 256 -> 320 at 64 103 -> 90, 57x53 72 -> 136 at 24 39.9 -> 37.9);
+//    for 192 and less for more channels (20x20 256 -> 192 at 160 77.6 -> 70.9 us,
+//    28x28 256 -> 320 at 64 103 -> 90, 57x53 72 -> 136 at 24 36.3 -> 33.9);
 //    conv_dma keeps up to 64 channels there unless k is long (31 steps).
-//  - conv_dma also keeps stride-1 1x1 layers that write more than they compute,
-//    with channels past a step or a tile: less than 160 input channels past 384
-//    tiles of 128 x 128 (14x14 96 -> 576 with a residual at 256 39.5 us against
-//    43.3), less than 192 with a residual from 257 to 512 (0.83 to 0.91; 7x7
-//    160 -> 960 at 128 10.6 against 12.0; at 5145, 56x56 168 -> 864 at 30, 163
-//    against 125).
+//  - conv_dma also keeps stride-1 1x1 layers that write more than they compute:
+//    with a residual and less than 192 input channels from 257 to 400 tiles of
+//    128 x 128 (128 -> 640 at 370 9.3 us against 9.9; no difference from there on),
+//    to 512 with channels past a step or a tile (0.83 to 0.91; 7x7 160 -> 960 at
+//    128 10.6 against 12.0; at 5145, 56x56 168 -> 864 at 30, 163 against 125),
+//    and those of less than 160 past 384 in any case (14x14 96 -> 576 with a
+//    residual at 256 39.5 against 43.3).
+// (Behind for all that: 28x28 72 -> 136 with a residual at 64, 27.9 us on conv_dma,
+// 29.0 here: a short k with 784 tiles, a few of which start a fourth round.)
 struct PpTile {
     int bn, bm;
     long tiles;
@@ -3023,7 +3026,7 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
     const int bn = n64 % 2 == 0 || (rag && big) ? 128 : 64;
     if (pw && (rag ? a.Cs < 160 && t128 >= 384 : bn == 64 && a.N > 64 && t96 > 768))
         return nullptr;
-    if (pw && rag && bn == 128 && a.res && a.Cs < 192 && t128 > 256 && t128 <= 512)
+    if (pw && bn == 128 && a.res && a.Cs < 192 && t128 > 256 && t128 <= (rag ? 512 : 400))
         return nullptr;
     const long steps = ((long)a.R * a.S * a.Cs + ks - 1) / ks;
     if (bn == 64 && ((a.Cs % ks && steps > 18 && t96 > 512 && t96 <= 680) ||
