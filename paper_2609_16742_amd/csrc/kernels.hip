@@ -862,8 +862,8 @@ __global__ __launch_bounds__(256) void splitk_reduce(ConvArgs a) {
 // was what bounded the kernel).  The next half step's fragments are read
 // under the current one's MFMAs, with one barrier a step between the two
 // halves.  Measured, four 16-channel waves -> this: 14x14x256 at batch 64
-// 32.2 -> 22.7 us, 14x14x512 at batch 32 54.5 -> 38.7, 7x7x512 at batch 64
-// 27.3 -> 25.3, 14x14x256 -> 7x7x512 24.2 -> 21.8.  The k loop runs plane by
+// 30.1 -> 20.6 us, 14x14x512 at batch 32 53.7 -> 34.3, 7x7x512 at batch 64
+// 24.7 -> 23.0, 14x14x256 -> 7x7x512 21.2 -> 18.8.  The k loop runs plane by
 // plane, taps inside a plane, so the sums are taken in another order than
 // conv_dma's; the epilogue (and the fused 2x2 pool) is conv_dma's.
 // ---------------------------------------------------------------------------
@@ -1088,8 +1088,8 @@ static hipError_t run_img(const ConvArgs &a, hipStream_t st) {
 // evenly over the waves; a wave crosses into the next strip where its part
 // does, and the ring runs on across that.
 // Measured (batch 32, conv_dma's halo tiles -> this): 224x224x64 with the pool
-// 176 -> 109 us, 112x112 64 -> 128 101 -> 59 us (1.0 PFLOP/s); 56x56x64 at 64
-// with a residual 31.4 -> 24.6.  What is left over is the matrix core at the
+// 151 -> 107 us, 112x112 64 -> 128 87 -> 52 us (1.13 PFLOP/s); 56x56x64 at 64
+// with a residual 29.7 -> 22.2.  What is left over is the matrix core at the
 // clock that its power allows and, on small maps, the filters' way into the
 // registers, about 3 us.
 // ---------------------------------------------------------------------------
@@ -1666,11 +1666,11 @@ __global__ __launch_bounds__(64 * SPLIT) void conv_lat(ConvArgs a) {
 // Per output, the MFMA sequence (k in order, two 16x16x32 MFMAs per 128-byte
 // row) is conv_dma's, so results are bit-identical.
 // Measured (batch 32, 3x3), eight waves alternating between reads and MFMAs
-// -> this: 56x56x256 132 -> 115 us, 28x28x512 123 -> 106 us (1.12 PFLOP/s),
-// 28x28 256 -> 512 70 -> 62 us.  With parts switched off in a copy, 28x28x512
-// takes 79 us for its MFMAs alone, 89 with the fragment reads, 95 with the
-// channel rows' and 104 with the pixel rows' DMAs as well; all-zero data
-// takes 10% less (the clock follows the power).
+// -> this: 56x56x256 127 -> 115 us, 28x28x512 121 -> 104 us (1.14 PFLOP/s),
+// 28x28 256 -> 512 65 -> 58 us, 56x56 128 -> 256 74 -> 69.  With parts switched off
+// in a copy, 28x28x512 took 79 us for its MFMAs alone, 89 with the fragment
+// reads, 95 with the channel rows' and 104 with the pixel rows' DMAs as well;
+// all-zero data took 10% less (the clock follows the power).
 //
 // Pixel tiles are TW == 0: BM consecutive output pixels in NHWC order, or
 // TW > 0: a (BM / TW) x TW block of one image (for the fused 2x2 max
@@ -2912,7 +2912,7 @@ static ConvCfg select_conv(int dt, const ConvArgs &a) {
         if (bm128 && a.pool && pool_waste_ok(a, 8, 16)) return D_128x64_P16;
         return bm128 ? D_128x64 : D_64x64;
     }
-    // (VGG-16 conv2_2 at batch 32 on conv_dma's loop 199 us, on conv_pp's 154)
+    // (VGG-16 conv2_2 at batch 32 on conv_dma's loop 168 us, on conv_pp's 126)
     if (bm128 && a.pool && pool_waste_ok(a, 8, 16))
         return a.Cs % 64 == 0 && a.N % 128 == 0 && pp_addr_ok(a, 2) ? PP_128_P16 : D_128x128_P16;
     return bm128 ? D_128x128 : D_64x128;
@@ -2938,19 +2938,19 @@ bool conv_pool_ok(int dt, const ConvArgs &a) {
 // `tiles` of them: more than one per CU for the largest, then smaller tiles
 // spread the pixels over more CUs.
 // conv_dma -> these, measured in graphs, fp16, 3x3: 28x28x128 at batch 8
-// 15.2 -> 9.3 us (32 pixels; 64: 10.6), 16 15.9 -> 11.2 (64), 32 19.2 -> 15.3
-// (64; 96: 16.4), 48 23.8 -> 19.7 (96); 28x28x512 at 16 78 -> 68 (128), 24 118
-// -> 106; 56x56 64 -> 128 stride 2 at 32 12.9 -> 10.5; 28x28 128 -> 256 stride
-// 2, 1x1, at 256 18.9 -> 15.9.  Channel counts that are no multiple of 128:
+// 14.4 -> 8.3 us (32 pixels), 16 14.7 -> 10.4 (64), 32 17.3 -> 13.7 (64), 48 21.8
+// -> 17.9 (96); 28x28x512 at 16 75 -> 65 (128), 24 119 -> 98; 56x56 64 -> 128
+// stride 2 at 32 11.5 -> 9.3; 28x28 128 -> 256 stride 2, 1x1, at 256 17.4 ->
+// 14.6.  Channel counts that are no multiple of 128:
 // 15x15x64 at batch 50 10.8 -> 6.5, 200 11.5 -> 9.7, 400 16.5 -> 16.2, 30x30
 // 128 -> 64 at 120 36.3 -> 31.7, 19x19 512 -> 64 at 33 47.1 -> 25.1.
-// 1x1: 7x7 320 -> 1280 at batch 128 15.5 -> 13.6 us, 2048 -> 512 at 64 23.4 ->
-// 17.6 (64 pixels), 14x14 512 -> 256 at 128 18.0 -> 15.2, 56x56 256 -> 512 at 64
-// 134 -> 121.
-// fp32: 28x28x128 at batch 64 145.9 -> 136.2 us, 14x14x256 163 -> 140 (64 x
-// 64: 150), 14x14 1024 -> 256 1x1 at 16 30.5 -> 24.4; many tiles with a short
-// k pay for the smaller tile's loads: 56x56x64 at 64 140.6 -> 133.4 (64 x 32:
-// 137.1), 56x56 64 -> 256 1x1 133 -> 121 (148).
+// 1x1: 7x7 320 -> 1280 at batch 128 13.8 -> 12.0 us, 2048 -> 512 at 64 21.8 ->
+// 15.7 (64 pixels), 14x14 512 -> 256 at 128 16.3 -> 13.8, 56x56 256 -> 512 at 64
+// 136 -> 121.
+// fp32: 28x28x128 at batch 64 146 -> 130 us, 14x14x256 162 -> 137 (64 x 64: 150),
+// 14x14 1024 -> 256 1x1 at 16 28.1 -> 21.7; many tiles with a short k pay for the
+// smaller tile's loads: 56x56x64 at 64 141 -> 130 (64 x 32: 137), 56x56 64 -> 256
+// 1x1 94 -> 85.
 // Lines between the fp16 tiles, from 6781 layers around them, mean and worst
 // gain over conv_dma:
 //  - Two 128 x 64 tiles share a CU.  Up to 256 tiles of 128 x 128 (512 of 128 x
