@@ -177,8 +177,7 @@ ctc_status ctc_conv2d_workspace_bytes(const ctc_layer_desc *desc,
  * name[cap].  With a workspace of ctc_conv2d_workspace_bytes a split layer
  * also launches splitk_reduce (or, in calls of a few images, splits inside
  * one kernel); with a residual a pooled layer of 64 input channels may run
- * another instance of its kernel, and a 1x1 layer of up to 32 input channels
- * another kernel.
+ * another instance of its kernel, and a stride-1 1x1 layer another kernel.
  * Host, synchronous.  Errors: as ctc_conv2d_forward's argument checks. */
 ctc_status ctc_conv2d_kernel_name(const ctc_layer_desc *desc, ctc_dtype dtype,
                                   int32_t n, int32_t h, int32_t w, int32_t pool,
