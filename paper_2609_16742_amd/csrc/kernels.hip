@@ -3061,7 +3061,8 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
 //    (conv_dma, 20%), or that waits on the filters (more than 3 MB, 15 to 75%;
 //    4 MB next to conv_ppr's 64-channel tiles); and, as its channel tiles are
 //    spread over the XCDs, where each XCD's L2 holds all of the input that is
-//    read (4 MB: 8 to 20% against -15%).
+//    read (4 MB: 8 to 20% against -15%; next to conv_dma's 32-channel tiles, 5705
+//    layers, 5 MB: 7 to 18%, or more than all L2s hold, 6%, against -14%).
 //  - The ranges of a split layer are four waves a tile: 512 tiles, 1024 with
 //    whole steps (fp32: 2048); 7x7x520 fp16 at 16 images (1617) 20.9 us against
 //    42.7 on conv_lat.
@@ -3077,6 +3078,7 @@ static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
     const long xbytes = (long)a.nimg * a.H * a.W * a.Cs * es, wbytes = a.N * K * es;
     if (a.Cs % (16 / es) || xbytes >= (1l << 31) || wbytes >= (1l << 31)) return false;
     const long M = (long)a.nimg * a.P * a.Q, nt = (a.N + 15) / 16, tiles = (M + 15) / 16 * nt;
+    const long xread = std::min(xbytes, M * K * es);     // input that the taps touch
     if (tiles > 2048) return false;
     if (c == IMG_14) return true;
     if (c == IMG_7 || c == IMG_7S2) return tiles <= 1024;
@@ -3100,14 +3102,14 @@ static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
         if (tiles > (K > 576 ? 1600 : a.N % 128 ? 512 : 1024)) return false;
         if (steps < (t->bn == 128 ? (whole ? 1 : 2) : whole ? 2 : 7)) return false;
         return !second || wbytes > (whole || t->bn == 128 ? 3000000 : 4000000) ||
-               (whole && (std::min(xbytes, M * K * es) < (4l << 20) ||
-                          (t->bn == 128 && tiles <= 1216)));
+               (whole && (xread < (4l << 20) || (t->bn == 128 && tiles <= 1216)));
     }
     if (a.N <= 32) {
         if (f32) return steps >= (!second ? (whole ? 1 : 2) : whole ? 3 : 7);
         if (!second) return whole || steps >= (a.R == 1 ? 2 : 4);
-        return steps >= 8 ? whole || tiles <= 1360 || nt == 1
-                          : whole && steps >= 4 && tiles <= 1360;
+        if (whole) return steps >= 8 ? a.R > 1 || tiles <= 1600 : steps >= 4 && tiles <= 1360;
+        if (nt == 1) return steps >= 4;
+        return steps >= 8 && (tiles <= 1360 || xread < (5l << 20) || xread > (32l << 20));
     }
     if (second) return steps >= (f32 ? 5 : 3);
     // (one step of fp16: conv_dma's 64 x 64 tiles of 3, 5 .. channel tiles)

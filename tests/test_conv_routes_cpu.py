@@ -28,6 +28,9 @@ LAT = [
     (("f16", 4, 28, 28, 128, 128, 3), True), (("f16", 1, 28, 28, 512, 512, 3), True),
     (("f32", 4, 14, 14, 260, 260, 3), True), (("f32", 5, 14, 14, 260, 260, 3), False),
     (("f32", 8, 14, 14, 256, 256, 3), True), (("f32", 12, 28, 28, 36, 40, 3), True),
+    # up to 32 channels: whole input in an L2, in none, past them all
+    (("f16", 4, 56, 56, 72, 32, 3), True), (("f16", 4, 56, 56, 264, 32, 3), False),
+    (("f16", 19, 49, 49, 664, 32, 3, 2), True), (("f16", 4, 56, 56, 264, 16, 3), True),
 ]
 
 
