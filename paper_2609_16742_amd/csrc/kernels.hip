@@ -3055,14 +3055,17 @@ static const PpTile *pp_tile(int dt, const ConvArgs &a, ConvCfg c) {
 //    tiles (14x14 96 -> 576 1x1, two steps, 3.5 us against 4.0 on conv_lat) and
 //    four of 3x3 next to conv_dma's 32-channel ones (72x72 16 -> 24, three
 //    steps, 4.6 against 4.9); three in fp32; two or one elsewhere.
-//  - Above, a SIMD's second wave costs what the first did.  It still is ahead
-//    of a kernel that runs a second round itself (fp32, more than 256 tiles of
-//    32 pixels x 64 channels: 20% against -9%), that has no tile for the layer
-//    (conv_dma, 20%), or that waits on the filters (more than 3 MB, 15 to 75%;
-//    4 MB next to conv_ppr's 64-channel tiles); and, as its channel tiles are
-//    spread over the XCDs, where each XCD's L2 holds all of the input that is
-//    read (4 MB: 8 to 20% against -15%; next to conv_dma's 32-channel tiles, 5705
-//    layers, 5 MB: 7 to 18%, or more than all L2s hold, 6%, against -14%).
+//  - Above, a SIMD's second wave costs what the first did (26700 layers of 1024 to
+//    2048 tiles).  conv_lat then is ahead of a kernel that has no tile for the layer
+//    (conv_dma: 20%), that runs a second round of its smallest tiles itself (fp32,
+//    past 256 of 32 pixels x 64 channels: 16 to 70%; else -10 to -25% with channels
+//    that end within a step) or whose filters outgrow an XCD's L2 (fp16, 3.5 MB:
+//    15 to 110%).  As its channel tiles are spread over the XCDs, each of these
+//    reads all of the input: where that fits its L2 too (4 to 6 MB), whole steps
+//    gain 5 to 27% in fp16 next to 128-channel tiles, 12% next to 64-channel ones up
+//    to 1300 tiles, and lose 6 to 28% where it does not.  Next to conv_dma's
+//    32-channel tiles it gains 7 to 18% up to 5 MB, or 6% past what all L2s hold,
+//    and loses 13% between.
 //  - The ranges of a split layer are four waves a tile: 512 tiles, 1024 with
 //    whole steps (fp32: 2048); 7x7x520 fp16 at 16 images (1617) 20.9 us against
 //    42.7 on conv_lat.
@@ -3089,20 +3092,25 @@ static bool lat_ok(int dt, const ConvArgs &a, ConvCfg c) {
     const bool whole = a.Cs % ks == 0, second = tiles > 1024;
     if (a.part && conv_splitk(dt, a) > 1) return tiles <= (!whole ? 512 : f32 ? 2048 : 1024);
     if (const PpTile *t = pp_tile(dt, a, c)) {
+        const long t32 = (M + 31) / 32 * ((a.N + 63) / 64);  // conv_pp's smallest tiles
         if (f32) {
             if (steps < (whole ? 2 : 3)) return false;
-            const bool rounds = (M + 31) / 32 * ((a.N + 63) / 64) > 256;
             if (!second) return true;
-            return whole ? steps > 31 || wbytes > 500000 || (rounds && steps > 2)
-                         : rounds && a.R > 1;
+            return whole ? steps > 2 && (t32 > 256 || (steps > 26 && xread < 7500000) ||
+                                         (wbytes > 500000 && xread < 6000000))
+                         : t32 > 256 && a.R > 1;
         }
         // (short in k: conv_pp's tiles of 128 and 64 channels are ahead from
         // 1024 and 512 tiles on: 56x56 64 -> 128 stride 2 6.3 us against 5.7 on
         // conv_lat at 784, 6.4 against 6.9 at 1568; 56x56x64 5.3, 5.7 at 784)
-        if (tiles > (K > 576 ? 1600 : a.N % 128 ? 512 : 1024)) return false;
+        const bool filters = wbytes > 3500000;
+        if (tiles > (filters ? 2048 : K > 576 ? 1600 : a.N % 128 ? 512 : 1024)) return false;
         if (steps < (t->bn == 128 ? (whole ? 1 : 2) : whole ? 2 : 7)) return false;
-        return !second || wbytes > (whole || t->bn == 128 ? 3000000 : 4000000) ||
-               (whole && (xread < (4l << 20) || (t->bn == 128 && tiles <= 1216)));
+        if (!second) return true;
+        if (filters) return whole || t->bn == 128 || t32 <= 200;
+        if (!whole) return false;
+        return t->bn == 128 ? t32 <= 195 || (steps > 10 && xread < 5500000)
+                            : tiles <= 1300 && steps > 17 && xread < 5000000;
     }
     if (a.N <= 32) {
         if (f32) return steps >= (!second ? (whole ? 1 : 2) : whole ? 3 : 7);
